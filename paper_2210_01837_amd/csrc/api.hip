@@ -566,11 +566,6 @@ int fcmdp_create_solver(const fcmdp_params* p, void* hip_stream,
     upload.to(&s->dct_f, Mf);
     upload.to(&s->dct_i, Pi);
     if (s->mixed) {
-      std::vector<float> mf(Mf.begin(), Mf.end()), pf(Pi.begin(), Pi.end());
-      upload.to(&s->dct_f32, mf);
-      upload.to(&s->dct_i32, pf);
-    }
-    if (s->mixed) {
       std::vector<float> q(Nz);
       for (int c = 0; c < Nz; ++c) q[c] = (float)(h2 * 0.5 * p->H * w[c]);
       upload.to(&s->quad, q);

@@ -27,6 +27,7 @@ struct ColParams {
   double scale;       // 1 / (Nx Ny)
   double kxs, kys;    // 2 pi / Lx, 2 pi / Ly
   const double* dctf; // forward Chebyshev transform [c][n] in FP64
+  double ie, s2H, hb; // 1 / eta, 2 / H, H / (4 eta)
 };
 
 // Column (kxi, nyi) of the exact low-wavenumber square |nx|, |ny| <= ns

@@ -142,8 +142,6 @@ struct fcmdp_solver {
   void* quad = nullptr;         // h^2 * Clenshaw-Curtis weights [Nz] (T)
   double* dct_f = nullptr;      // forward Chebyshev transform, [c][n]
   double* dct_i = nullptr;      // inverse, T_n(s_c), [c][n]
-  float* dct_f32 = nullptr;     // float copies for the MFMA transforms
-  float* dct_i32 = nullptr;
   double* dftc = nullptr;       // cos/sin tables of the small prime DFTs
   void* tw_x = nullptr;         // e^{-2 pi i m/(Nx/2)}, m < Nx/2 (complex T)
   void* tw_y = nullptr;         // e^{-2 pi i m/Ny}
@@ -159,7 +157,7 @@ struct fcmdp_solver {
   int codelet_x = -1, codelet_y = -1;   // fixed-plan kernels, -1 = none
   void* dftc_t = nullptr;       // dftc converted to T
 
-  // use the one-thread-per-column solver even when Nz <= 32 (tests)
+  // use the one-thread-per-column solver (tests)
   bool force_generic_columns = false;
   // use the one-thread-per-particle interpolation (tests)
   bool force_simple_interp = false;
@@ -242,10 +240,10 @@ int fft_codelet(int n, bool fp32, FFTPlan* plan, int* tpr);
 // with room for the Nyquist element; y: Ny) for fixed plan `codelet` (-1:
 // run-time plan)
 int fft_lds_row(int codelet, int n, bool x);
-// columns.hip (dispatches to columns_seg.hip for Nz <= 32)
+// columns.hip (one thread per column, a cross-check); columns_mfma.hip
 hipError_t launch_columns(const fcmdp_solver* s, const void* spec_in,
                           void* spec_out, hipStream_t st);
-hipError_t launch_columns_seg(const fcmdp_solver* s, const void* spec_in,
+hipError_t launch_columns_mfma(const fcmdp_solver* s, const void* spec_in,
                               void* spec_out, hipStream_t st);
 
 // --- small device helpers ------------------------------------------------
