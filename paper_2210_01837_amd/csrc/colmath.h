@@ -24,10 +24,10 @@ __device__ inline Z2 imul(double s, Z2 a) { return zmk(-s * a.y, s * a.x); }
 
 struct ColParams {
   DevParams dp;
-  double scale;       // 1 / (Nx Ny)
+  double scale;       // 1 / (Nx Ny); over eta in columns_mfma.hip
   double kxs, kys;    // 2 pi / Lx, 2 pi / Ly
   const double* dctf; // forward Chebyshev transform [c][n] in FP64
-  double ie, s2H, hb; // 1 / eta, 2 / H, H / (4 eta)
+  double iH, s2H;     // 1 / H, 2 / H
 };
 
 // Column (kxi, nyi) of the exact low-wavenumber square |nx|, |ny| <= ns

@@ -114,113 +114,118 @@ __device__ __forceinline__ double frcp(double x) {
   return fma(r, e, r);
 }
 
-// Rows m = 2 i + parity >= 2 of B^2 (times H^2 / 4) and of B:
-//   tl = (H^2/4) / (4 m (m - 1)), tu = (H^2/4) / (4 m (m + 1)), hm = H / (4 m),
-// zero for m >= N, and m2 = m^2: (H^2/4)(B^2 r)_m = tl (c_{m-2} r_{m-2} - r_m) - tu (r_m -
-// r_{m+2}), and (H^2/4) B^2 (f') is hm (f_{m-1} - f_{m+1}).
-// The rows of both parities lie in LDS: [2 NA] pairs (tl, tu), then hm, then m2.
-template <int NA> struct RowTab {
-  double2 t[2 * NA];
-  double hm[2 * NA], m2[2 * NA];
-};
-// Table rows are read where they are used: the offset is opaque to the
+// Value of lane xor 32, through the LDS crossbar (no vector instruction).
+__device__ __forceinline__ float pass(float x, int addr) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(x)));
+}
+__device__ __forceinline__ double pass(double x, int addr) {
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(addr, __double2hiint(x)),
+                          __builtin_amdgcn_ds_bpermute(addr, __double2loint(x)));
+}
+
+// Rows of the double antiderivative, m = 2 i + parity >= 2, divided by their
+// first entry tl = (H^2/4) / (4 m (m - 1)):
+//   (H^2/4)(B^2 f)_m  = tl (d_i - rho d_{i+1}),  d_i = c_{m-2} f_{m-2} - f_m,
+//                       rho = (m - 1) / (m + 1)
+//   (H^2/4)(B^2 f')_m = tl (4/H)(m - 1)(f_{m-1} - f_{m+1}).
+// tl = rho = 0 for m >= N.  The rows of both parities lie in LDS.
+// Table rows are read where they are used: the address is opaque to the
 // optimiser at every use, so that the reads are neither hoisted out of the
 // column loop nor kept in registers from one sweep to the next (the scheduling
 // barrier keeps the sweeps from being interleaved for the same reason).
+typedef __attribute__((address_space(3))) const double* LdsPtr;
+template <int NA> struct RowTab {
+  double v[2][5][NA];             // [parity]: rho, tl, m - 1, m^2, m
+};
 template <int NA> struct Rows {
-  const RowTab<NA>* tab;
-  int off;                        // parity * NA
-  __device__ __forceinline__ double2 t(int i) const { return tab->t[off + i]; }
-  __device__ __forceinline__ double hm(int i) const { return tab->hm[off + i]; }
-  __device__ __forceinline__ double m2(int i) const { return tab->m2[off + i]; }
+  LdsPtr p;
+  __device__ __forceinline__ double rho(int i) const { return p[i]; }
+  __device__ __forceinline__ double tl(int i) const { return p[NA + i]; }
+  __device__ __forceinline__ double m1(int i) const { return p[2 * NA + i]; }
+  __device__ __forceinline__ double m2(int i) const { return p[3 * NA + i]; }
+  __device__ __forceinline__ double n(int i) const { return p[4 * NA + i]; }
 };
 template <int NA>
 __device__ __forceinline__ Rows<NA> fresh(const RowTab<NA>& tab, int off) {
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" : "+v"(off));
-  return Rows<NA>{&tab, off};
-}
-// this lane's parity, opaque like fresh(): the weights n and n^2 of the series
-// are formed where they are used
-__device__ __forceinline__ double parity(bool up) {
-  double p = up ? 1.0 : 0.0;
+  LdsPtr p = (LdsPtr)&tab.v[0][0][0] + off;
   asm volatile("" : "+v"(p));
-  return p;
+  return Rows<NA>{p};
 }
 
 // Coefficients n = 2 i + parity of one real column, NA per lane.
 // The tridiagonal half of y - k^2 (H^2/4) B^2 y = R with the dense boundary
 // row sum_i e_i y_i = g (e_i = m^2 + kappa), eliminated from the last
-// coefficient: y_i = al_i y_{i-1} + be_i.  c_i = e_i + al_{i+1} c_{i+1}, the
-// weight that y_i carries in sum_{j >= i} e_j y_j, is recomputed in each
-// solve: two operations per row instead of 2 NA registers.
+// coefficient.  With R_i = k^2 tl_i r_i (the callers form r, scaled so that
+// one of its series needs no factor) and al_i = k^2 tl_i / Delta_i:
+//   s_i = r_i + rho_i be_{i+1},  be_i = al_i s_i,  y_i = al_i (c y_{i-1} + s_i)
+// and c_i = e_i + al_{i+1} c_{i+1} is the weight that y_i carries in
+// sum_{j >= i} e_j y_j: five operations per row and right-hand side.
 template <int NA> struct HalfOp {
-  double al[NA], iv[NA];          // entries 1 .. NA - 1
+  double al[NA], c[NA];           // entries 1 .. NA - 1
   double ic0;
 
-  __device__ __forceinline__ void prepare(Rows<NA> rows, double k2, double kappa,
-                                          bool up) {
+  __device__ __forceinline__ void prepare(Rows<NA> rows, double k2, double kappa, bool up) {
     double aln = 0.0, cn = 0.0;
 #pragma unroll
     for (int i = NA - 1; i >= 1; --i) {
-      const double tl = rows.t(i).x, tu = rows.t(i).y;
-      const double d = fma(-(k2 * tu), aln, fma(k2, tl + tu, 1.0));
+      const double t = k2 * rows.tl(i), rho = rows.rho(i);
       cn = fma(aln, cn, rows.m2(i) + kappa);
-      iv[i] = frcp(d);
-      double a = k2 * tl * iv[i];
-      if (i == 1) a = up ? a : 2.0 * a;             // c_{m-2} = 2 for m = 2
-      al[i] = a;
-      aln = a;
+      aln = t * frcp(fma(t, fma(-rho, aln, 1.0 + rho), 1.0));
+      al[i] = aln;
+      c[i] = cn;
     }
-    ic0 = frcp(fma(aln, cn, (up ? 1.0 : 0.0) + kappa));   // e_0, e_1 = 0, 1 plus kappa
+    // c_{m-2} = 2 for m = 2; e_0, e_1 = 0, 1 plus kappa
+    ic0 = frcp(fma(up ? aln : 2.0 * aln, cn, (up ? 1.0 : 0.0) + kappa));
   }
-  // y: R_1 .. R_{NA-1} on entry, the solution on return
-  __device__ __forceinline__ void solve(Rows<NA> rows, double k2, double kappa,
-                                        double* y, double g) const {
-    double b = 0.0, c = 0.0;
+  // y: r_1 .. r_{NA-1} on entry, the solution on return
+  __device__ __forceinline__ void solve(Rows<NA> rows, double* y, double g, bool up) const {
+    double b = 0.0;
 #pragma unroll
     for (int i = NA - 1; i >= 1; --i) {
-      b = iv[i] * fma(k2 * rows.t(i).y, b, y[i]);
-      y[i] = b;
-      const double e = rows.m2(i) + kappa;
-      c = i == NA - 1 ? e : fma(al[i + 1 < NA ? i + 1 : i], c, e);
-      g = fma(-c, b, g);
+      y[i] = fma(rows.rho(i), b, y[i]);
+      b = al[i] * y[i];
+      g = fma(-c[i], b, g);
     }
     y[0] = g * ic0;
+    y[1] = al[1] * fma(up ? 1.0 : 2.0, y[0], y[1]);
 #pragma unroll
-    for (int i = 1; i < NA; ++i) y[i] = fma(al[i], y[i - 1], y[i]);
+    for (int i = 2; i < NA; ++i) y[i] = al[i] * (y[i - 1] + y[i]);
   }
 };
 
-// out_i += s (H^2/4)(B^2 f)_i and s hm_i (f_{m-1} - f_{m+1}) with the other
-// parity's series, rows 1 .. NA - 1; f(i) is this lane's coefficient i
-template <int NA, typename F>
-__device__ __forceinline__ void add_b2(Rows<NA> rows, double s, const F& f, bool up,
-                                       double* out) {
-  double prev = f(0);
-  prev = up ? prev : 2.0 * prev;
+// rows 1 .. NA - 1 of the two kinds of right-hand side (f(i): this lane's
+// coefficient i); SET: out = , else out +=; NEG: minus
+template <int NA, bool SET, bool NEG, typename F>
+__device__ __forceinline__ void add_b2(Rows<NA> rows, const F& f, bool up, double* out) {
+  const double f0 = f(0);
   double cur = f(1);
+  double d = (up ? f0 : 2.0 * f0) - cur;
 #pragma unroll
   for (int i = 1; i < NA; ++i) {
-    const double next = i + 1 < NA ? f(i + 1) : 0.0;
-    const double2 w = rows.t(i);
-    const double v = fma(w.x, prev - cur, -(w.y * (cur - next)));
-    out[i] = fma(s, v, out[i]);
-    prev = cur;
+    const double next = i + 1 < NA ? f(i + 1 < NA ? i + 1 : i) : 0.0;
+    const double dn = cur - next;
+    const double v = NEG ? fma(rows.rho(i), dn, -d) : fma(-rows.rho(i), dn, d);
+    out[i] = SET ? v : out[i] + v;
     cur = next;
+    d = dn;
   }
 }
-template <int NA, typename F>
-__device__ __forceinline__ void add_b(Rows<NA> rows, double s, const F& f, bool up,
+template <int NA, bool SET, bool NEG, typename F>
+__device__ __forceinline__ void add_b(Rows<NA> rows, const F& f, bool up, int addr,
                                       double* out) {
   using V = decltype(f(0));
-  double cur = (double)across(f(0), f(1), up);
+  // row i needs the other parity's coefficients i - 1, i (even m) or i, i + 1
+  V h[NA];
+#pragma unroll
+  for (int i = 1; i <= NA; ++i) {
+    const V z = V(0);
+    h[i - 1] = pass(up ? f(i - 1) : (i < NA ? f(i < NA ? i : 0) : z), addr);
+  }
 #pragma unroll
   for (int i = 1; i < NA; ++i) {
-    const V z = V(0);
-    const double next = (double)across(f(i), i + 1 < NA ? f(i + 1) : z, up);
-    out[i] = fma(s * rows.hm(i), cur - next, out[i]);
-    cur = next;
+    const double d = (double)h[i - 1] - (double)h[i];
+    out[i] = SET ? rows.m1(i) * d : fma(NEG ? -rows.m1(i) : rows.m1(i), d, out[i]);
   }
 }
 template <int NA>
@@ -244,29 +249,24 @@ __device__ __forceinline__ void wall_sums(const double* y, bool up, double& top,
 // z-derivative sums in units of 2/H: top = sum n^2 a_n, bot = sum (-1)^(n+1)
 // n^2 a_n
 template <int NA>
-__device__ __forceinline__ void wall_dsums(const double* y, bool up, double& top,
-                                           double& bot) {
-  const double pf = parity(up);
+__device__ __forceinline__ void wall_dsums(Rows<NA> rows, const double* y, bool up,
+                                           double& top, double& bot) {
   double s = 0.0;
 #pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const double n = 2.0 * i + pf;
-    s = fma(n * n, y[i], s);
-  }
+  for (int i = 0; i < NA; ++i) s = fma(rows.m2(i), y[i], s);
   const double o = across(s, s, up);
   top = s + o;
   bot = up ? s - o : o - s;
 }
-// k = 0: y'' = r; y holds R_1 .. R_{NA-1} (the coefficients m >= 2 of the
-// solution).  Bottom wall: y(0) - l_0 y'(0) = g0, y'(H) = 0; slit channel:
+// k = 0: y'' = r; y holds the coefficients m >= 2 of the solution.  Bottom wall: y(0) - l_0 y'(0) = g0, y'(H) = 0; slit channel:
 // y(0) - l_0 y'(0) = g0, y(H) + l_H y'(H) = gH (a = 2 l / H).
 template <int NA, int GEOM>
-__device__ __forceinline__ void zero_mode(double* y, bool up, double a0, double aH,
+__device__ __forceinline__ void zero_mode(Rows<NA> rows, double* y, bool up, double a0, double aH,
                                           double g0, double gH) {
   y[0] = 0.0;
   double sp, sm, sn2, sdm;
   wall_sums<NA>(y, up, sp, sm);
-  wall_dsums<NA>(y, up, sn2, sdm);
+  wall_dsums<NA>(rows, y, up, sn2, sdm);
   if constexpr (GEOM == 0) {
     y[0] = up ? -sn2 : -sn2 - sm + g0 + a0 * (sdm - sn2);
   } else {
@@ -274,43 +274,54 @@ __device__ __forceinline__ void zero_mode(double* y, bool up, double a0, double 
     y[0] = up ? y1 : gH - sp - aH * sn2 - (1.0 + aH) * y1;
   }
 }
-// a_n -> (2/H) d/dz: b_m = c_m (4/H) sum over n > m of the other parity of
-// n a_n, c_0 = 1/2; own suffix sums, rounded to the transform's type and
-// exchanged
+// out_m = s c_m sum over n > m of the other parity of n a_n, c_0 = 1/2 (the
+// series of the derivative for s = 4 / H): own suffix sums, rounded to the
+// transform's type and exchanged
 template <int NA, typename D>
-__device__ __forceinline__ void derivative(const double* y, bool up, double s, D* out) {
-  const double pf = parity(up);
+__device__ __forceinline__ void derivative(Rows<NA> rows, const double* y, bool up, int addr,
+                                           double s, D* out) {
   double sum = 0.0;
   D after = D(0);
 #pragma unroll
   for (int i = NA - 1; i >= 0; --i) {
-    sum = fma(2.0 * i + pf, y[i], sum);
+    sum = fma(rows.n(i), y[i], sum);
     const D here = (D)(s * sum);
     // even outputs 2 i: odd terms from i on; odd outputs: even terms from i + 1
-    D v = across(here, after, up);
-    if (i == 0) v = up ? v : D(0.5) * v;
-    out[i] = v;
+    const D v = pass(up ? here : after, addr);
+    out[i] = i == 0 && !up ? D(0.5) * v : v;
     after = here;
   }
 }
 
-// s - 2 q e^{-q} with s = 1 - e^{-2 q}, i.e. 2 e^{-q} (sinh q - q), without
-// the cancellation at small q
-__device__ __forceinline__ double sinh_excess(double q, double E, double s) {
-  if (q >= 1.0) return s - 2.0 * q * E;
-  const double q2 = q * q;
-  // q^3/3! + q^5/5! + ... + q^19/19!
-  double t = 0.0;
-  const double d[9] = {6, 20, 42, 72, 110, 156, 210, 272, 342};
+// For q > 0: E = e^{-q}, s = 1 - E^2 and ex = s - 2 q E = 2 E (sinh q - q), the
+// last two without cancellation at small q.  Taylor coefficients f[j] = 1 / j!
+// from LDS (as constants of the library function they would be kept in
+// registers over the whole column loop).
+__device__ __forceinline__ void wall_decay(LdsPtr f, double q, double& E, double& s,
+                                           double& ex) {
+  asm volatile("" : "+v"(f));
+  // e^{-q} = 2^{-n} e^{-r}, |r| <= ln 2 / 2: 0.347^14 / 14! < 5e-18
+  const double n = rint(q * 1.4426950408889634074);
+  double r = fma(-n, 0x1.62e42fefa39efp-1, q);
+  r = fma(-n, 0x1.abc9e3b39803fp-56, r);
+  double p = f[13];
 #pragma unroll
-  for (int j = 8; j >= 0; --j) t = q2 / d[j] * (1.0 + t);
-  return 2.0 * E * q * t;
+  for (int j = 12; j >= 0; --j) p = fma(-r, p, f[j]);
+  E = ldexp(p, -(int)n);
+  const double q2 = q * q;
+  double t = f[19];                                 // (sinh q - q) / q^3
+#pragma unroll
+  for (int j = 8; j >= 1; --j) t = fma(q2, t, f[2 * j + 1]);
+  t *= q2;
+  const bool small = q < 1.0;
+  s = small ? 2.0 * E * q * (1.0 + t) : fma(-E, E, 1.0);
+  ex = small ? 2.0 * E * q * t : fma(-2.0 * q, E, s);
 }
 
 template <typename T, typename D, int NT, int NA, int GEOM, bool TIN, bool WOUT>
 __global__ void __launch_bounds__(256, sizeof(D) == 4 ? 2 : 1)
-k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
-               cplx_t<T>* out, const double* __restrict__ zc,
+k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
+               const cplx_t<T>* in, cplx_t<T>* out, const double* __restrict__ zc,
                const double* __restrict__ Mf, const double* __restrict__ Pi) {
   using C = cplx_t<T>;
   using M = Mat<D>;
@@ -326,11 +337,18 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
   constexpr int kPark = sizeof(D) == 4 ? (TIN ? 2 : 1) * NA : 0;
   __shared__ D parked[kPark ? 4 * kPark * 64 : 1];
   __shared__ D zn[2 * NA];
+  __shared__ double fact[GEOM == 1 ? 20 : 1];      // 1 / j!
   const DevParams& dp = cp.dp;
   const int lo = band[0], hi = band[1];
   if (lo > hi) return;
   const int N = dp.Nz;
   const double H = dp.H;
+  // node tiles of 16 of the inverse transform, and whether the last one to four
+  // nodes take the 4 x 4 products
+  constexpr bool kTail = sizeof(D) == 4;
+  const int P = hi - lo + 1;
+  const bool tail = kTail && P % 16 >= 1 && P % 16 <= 4;
+  const int tiles = tail ? P / 16 : (P + 15) / 16;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // --- tables ---------------------------------------------------------------
@@ -343,21 +361,29 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       const int n = 2 * ((g & 1) * kHalf + j) + (g >> 1), c = 4 * s + g4;
       mf[e] = (j < kHalf && n < N && c < N) ? (D)Mf[c * N + n] : D(0);
     }
-    // inverse: row -> band node; column -> coefficient s of group g4
+    // inverse: row -> band node; column -> coefficient s of group g4 (the 4 x 4
+    // tail takes its rows from lane % 4)
     {
-      const int n = 2 * ((g4 & 1) * kHalf + s) + (g4 >> 1), c = lo + 16 * t + row;
+      const int n = 2 * ((g4 & 1) * kHalf + s) + (g4 >> 1);
+      const int c = lo + 16 * t + (kTail && tail && t == tiles ? l & 3 : row);
       pi[e] = (n < N && c <= hi) ? (D)Pi[c * N + n] : D(0);
     }
   }
   for (int e = tid; e < 2 * NA; e += 256) {
     const int p = e / NA, m = 2 * (e % NA) + p;
     const bool row = m >= 2 && m < N;
-    const double h2 = 0.25 * H * H;
-    tabs.t[e] = row ? make_double2(h2 / (4.0 * m * (m - 1.0)), h2 / (4.0 * m * (m + 1.0)))
-                    : make_double2(0.0, 0.0);
-    tabs.hm[e] = row ? H / (4.0 * m) : 0.0;
-    tabs.m2[e] = (double)m * m;
+    double(*v)[NA] = tabs.v[p];
+    v[0][e % NA] = row ? (m - 1.0) / (m + 1.0) : 0.0;
+    v[1][e % NA] = row ? 0.25 * H * H / (4.0 * m * (m - 1.0)) : 0.0;
+    v[2][e % NA] = m - 1.0;
+    v[3][e % NA] = (double)m * m;
+    v[4][e % NA] = m;
     zn[e] = e < N ? (D)zc[e] : D(0);
+  }
+  if (GEOM == 1 && tid < 20) {
+    double f = 1.0;
+    for (int j = 2; j <= tid; ++j) f *= j;
+    fact[tid] = 1.0 / f;
   }
   __syncthreads();
 
@@ -367,12 +393,58 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
   const int col = lane & 15, g4 = lane >> 4;
   const bool up = lane >= 32;                      // odd parity
   const bool imag = (lane & 16) != 0;
-  const int toff = up ? NA : 0;
-  const double ie = cp.ie, s2H = cp.s2H;
+  const int toff = up ? 5 * NA : 0;
+  const double s2H = cp.s2H;
+  const int xaddr = (lane ^ 32) * 4;               // for pass()
   const double l0 = dp.slip0, lH = GEOM == 1 ? dp.slipH : 0.0;
   const bool slip = l0 != 0.0 || lH != 0.0;        // uniform
   const int s_lo = lo / 4, s_hi = hi / 4;
-  for (int grp = blockIdx.x * 4 + wave; grp < G; grp += gridDim.x * 4) {
+  // the first steps of a group's band values are loaded while the inverse
+  // transform of the group before it runs (FP32 transforms: the registers are
+  // there)
+  constexpr int kCh = 5;                           // steps in flight
+  // (part L takes all but G_z, part T all but F_z)
+  auto fetch = [&](C (&w)[kCh][kNin], int grp, int s0, bool part_l, bool part_t) {
+    const int idc = min(grp * 16 + col, K - 1);
+#pragma unroll
+    for (int u = 0; u < kCh; ++u) {
+      const int c = min(max(4 * (s0 + u) + g4, lo), hi);
+      const C* src = in + (size_t)c * PS + idc;
+#pragma unroll
+      for (int ch = 0; ch < kNin; ++ch) w[u][ch].x = w[u][ch].y = T(0);
+      if (s0 + u <= s_hi) {                        // uniform
+#pragma unroll
+        for (int ch = 0; ch < kNin; ++ch)
+          if ((part_l || ch != 2) && (part_t || ch != 5)) w[u][ch] = src[(size_t)ch * N * PS];
+      }
+    }
+  };
+  // LOW: the column groups that hold columns of the low-wavenumber square
+  // (their own workgroups and their own copy of the code, so that the FP64
+  // route's registers do not weigh on the other groups)
+  auto run = [&](auto low_tag) __attribute__((always_inline)) {
+  constexpr bool LOW = decltype(low_tag)::value;
+  constexpr bool kAhead = sizeof(D) == 4 && !LOW && false;
+  const int ns = dp.lowk_ns;
+  int grp, stride, last;
+  if constexpr (LOW) {
+    // wave w takes group w % per of the range of columns kx Ny - ns .. kx Ny +
+    // ns, kx = w / per; a group met by the range before is left to it
+    const int per = ns / 8 + 2, w = blockIdx.x * 4 + wave, q = w / per;
+    if (q > ns + 1) return;
+    const int first = max(q * dp.Ny - ns, 0) / 16;
+    grp = first + w % per;
+    stride = G;
+    last = min((q * dp.Ny + ns) / 16, G - 1) + 1;
+    if (q > 0 && grp <= ((q - 1) * dp.Ny + ns) / 16) return;
+  } else {
+    grp = (blockIdx.x - low_blocks) * 4 + wave;
+    stride = (gridDim.x - low_blocks) * 4;
+    last = G;
+  }
+  C w[kCh][kNin];
+  if (kAhead && grp < last) fetch(w, grp, s_lo, true, true);
+  for (; grp < last; grp += stride) {
     int ln = lane;                                 // (opaque, as in fresh())
     asm volatile("" : "+v"(ln));
     const int idx = grp * 16 + col;
@@ -385,52 +457,40 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
     const double k = sqrt(fma(kx, kx, ky * ky));
     const bool zero = k == 0.0;                    // the mean flow's column
     const bool zero_grp = grp == 0;                // (uniform)
-    const double kp = zero ? 1.0 : k, ik = frcp(kp);
+    // Units: p times k^2 H/4, U and T times cU = eta k^2 H/4, W times cW = eta
+    // (k^2 H/4)^2 make the derivative terms of every right-hand side enter with
+    // factor one; the inverse goes into the output scale.  The mean flow takes
+    // a k so small that the sweeps return its rows m >= 2 as they are.
+    const double kp = zero ? 1e-9 * cp.s2H : k, ik = frcp(kp);
     const double cx = zero ? 1.0 : kx * ik, cy = ky * ik;
-    // k = 0: with a zero k2 the sweeps return the rows m >= 2 as they are
-    const double k2 = zero ? 0.0 : kp * kp, kappa = 0.5 * kp * H;
+    const double k2 = kp * kp, kappa = zero ? 1.0 : 0.5 * kp * H;
+    const double cWU = 0.25 * H * k2, cUW = 4.0 * cp.iH * ik * ik;   // cW / cU and inverse
     int lcol = -1;
-    bool low_grp = false;
     if constexpr (kLow) {
-      lcol = nyq ? -1 : lowk_col(dp, kxi, nyi);
-      low_grp = __any(lcol >= 0);
+      lcol = nyq || !valid ? -1 : lowk_col(dp, kxi, nyi);
+      if ((__any(lcol >= 0) != 0) != LOW) {
+        if (kAhead && grp + stride < last) fetch(w, grp + stride, s_lo, true, true);
+        continue;
+      }
     }
 
     // --- forward transform of the band nodes ---------------------------------
-    // vectors: i F_L, F_z, gamma (part L) and F_T - (1/2) i k G_z, G_L (T)
+    // vectors: i F_L, F_z, gamma / 2 (part L), F_T - (1/2) i k G_z, G_L / 2 (T)
     D aL[NA], aZ[NA], aG[TIN ? NA : 1], aT[NA], aH[TIN ? NA : 1];
     D* const park = &parked[(size_t)wave * kPark * 64 + lane];
     auto forward = [&](auto part_l, auto part_t) {
       constexpr bool PL = decltype(part_l)::value, PT = decltype(part_t)::value;
       constexpr int nL = PL ? (TIN ? 3 : 2) : 0, nT = PT ? (TIN ? 2 : 1) : 0;
       constexpr int nV = nL + nT;
-      constexpr int kCh = 5;                        // steps in flight
       Acc acc[nV][2][NT];
 #pragma unroll
       for (int v = 0; v < nV; ++v)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[v][0][t] = acc[v][1][t] = Acc{0, 0, 0, 0};
       const D dcx = (D)cx, dcy = (D)cy, hk = (D)(0.5 * k);
+      const D hcx = (D)(0.5 * cx), hcy = (D)(0.5 * cy);
       for (int s0 = s_lo; s0 <= s_hi; s0 += kCh) {
-        C w[kCh][kNin];
-#pragma unroll
-        for (int u = 0; u < kCh; ++u) {
-          const int c = 4 * (s0 + u) + g4;
-          const int cc = min(max(c, lo), hi);
-          const bool use = s0 + u <= s_hi;          // uniform
-          const C* src = in + (size_t)cc * PS + idc;
-#pragma unroll
-          for (int ch = 0; ch < kNin; ++ch) {
-            w[u][ch].x = w[u][ch].y = T(0);
-          }
-          if (use) {
-#pragma unroll
-            for (int ch = 0; ch < kNin; ++ch) {
-              // part L takes all but G_z, part T all but F_z
-              if ((PL || ch != 2) && (PT || ch != 5)) w[u][ch] = src[(size_t)ch * N * PS];
-            }
-          }
-        }
+        if (!kAhead || s0 > s_lo) fetch(w, grp, s0, PL, PT);
 #pragma unroll
         for (int u = 0; u < kCh; ++u) {
           if (s0 + u > s_hi) break;                 // uniform
@@ -449,8 +509,8 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
             xr[1] = fr[2];
             xi[1] = fi[2];
             if constexpr (TIN) {
-              xr[2] = -fma(dcx, fi[4], -(dcy * fi[3]));
-              xi[2] = fma(dcx, fr[4], -(dcy * fr[3]));
+              xr[2] = -fma(hcx, fi[4], -(hcy * fi[3]));
+              xi[2] = fma(hcx, fr[4], -(hcy * fr[3]));
             }
           }
           if constexpr (PT) {
@@ -459,8 +519,8 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
             if constexpr (TIN) {
               xr[nL] = fma(hk, fi[5], xr[nL]);
               xi[nL] = fma(-hk, fr[5], xi[nL]);
-              xr[nL + 1] = fma(dcx, fr[3], dcy * fr[4]);
-              xi[nL + 1] = fma(dcx, fi[3], dcy * fi[4]);
+              xr[nL + 1] = fma(hcx, fr[3], hcy * fr[4]);
+              xi[nL + 1] = fma(hcx, fi[3], hcy * fi[4]);
             }
           }
 #pragma unroll
@@ -522,9 +582,12 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
         }
         if (zero) {
           const double nxy = (double)dp.Nx * (double)dp.Ny;
-          x = zmk(x.x + nxy * w[0], 0);
-          y = zmk(y.x + nxy * w[1], 0);
+          x = zmk(fma(nxy, w[0], x.x), 0);
+          y = zmk(fma(nxy, w[1], y.x), 0);
         }
+        const double c = dp.eta * cWU;              // cU
+        x = c * x;
+        y = c * y;
         wu = imag ? cx * x.x + cy * y.x : -(cx * x.y + cy * y.y);
         wt = imag ? cx * y.y - cy * x.y : cx * y.x - cy * x.x;
       };
@@ -535,10 +598,10 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
     }
     // (the k = 0 column has its own first coefficients)
     auto solve = [&](double* y, double g, double g0, double gH) {
-      op.solve(fresh(tabs, toff), k2, kappa, y, g);
+      op.solve(fresh(tabs, toff), y, g, up);
       if (zero_grp) {
         const double y0 = y[0];
-        zero_mode<NA, GEOM>(y, up, l0 * s2H, lH * s2H, g0, gH);
+        zero_mode<NA, GEOM>(fresh(tabs, toff), y, up, l0 * s2H, lH * s2H, g0, gH);
         y[0] = zero ? y[0] : y0;
       }
     };
@@ -572,54 +635,53 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       }
     };
     double U[NA], W[NA], Y[NA];                     // U holds p first
-#pragma unroll
-    for (int i = 0; i < NA; ++i) U[i] = 0.0;
-    add_b2<NA>(fresh(tabs, toff), k, [&](int i) { return (double)aL[i]; }, up, U);
-    if (kLow && low_grp) {
+    {
+      const double f = 0.25 * H * k;
+      add_b2<NA, true, false>(fresh(tabs, toff), [&](int i) { return f * (double)aL[i]; }, up,
+                              U);
+    }
+    if constexpr (LOW) {
       double f[NA];
       low_fz(f);
-      add_b<NA>(fresh(tabs, toff), 1.0, [&](int i) { return f[i]; }, up, U);
+      add_b<NA, false, false>(fresh(tabs, toff), [&](int i) { return f[i]; }, up, xaddr, U);
     } else {
-      add_b<NA>(fresh(tabs, toff), 1.0, [&](int i) { return aZ[i]; }, up, U);
+      add_b<NA, false, false>(fresh(tabs, toff), [&](int i) { return aZ[i]; }, up, xaddr, U);
     }
     op.prepare(fresh(tabs, toff), k2, kappa, up);
     solve(U, 0.0, 0.0, 0.0);
     const double pS = own_sum<NA>(U), pO = across(pS, pS, up);
     // W
-#pragma unroll
-    for (int i = 0; i < NA; ++i) W[i] = 0.0;
-    if (kLow && low_grp) {
-      double f[NA];
-      low_fz(f);
-      add_b2<NA>(fresh(tabs, toff), -ie, [&](int i) { return f[i]; }, up, W);
-    } else {
-      add_b2<NA>(fresh(tabs, toff), -ie, [&](int i) { return (double)aZ[i]; }, up, W);
+    add_b<NA, true, false>(fresh(tabs, toff), [&](int i) { return U[i]; }, up, xaddr, W);
+    {
+      const double fz = 0.25 * kappa * kappa, fg = fz * k;
+      auto force = [&](double z, int i) {
+        if constexpr (TIN) return fma(fg, (double)aG[i], fz * z);
+        else return fz * z;
+      };
+      if constexpr (LOW) {
+        double f[NA];
+        low_fz(f);
+        add_b2<NA, false, true>(fresh(tabs, toff), [&](int i) { return force(f[i], i); }, up,
+                                W);
+      } else {
+        add_b2<NA, false, true>(fresh(tabs, toff),
+                                [&](int i) { return force((double)aZ[i], i); }, up, W);
+      }
+      solve(W, fz * pO, 0.0, 0.0);
     }
-    add_b<NA>(fresh(tabs, toff), ie, [&](int i) { return U[i]; }, up, W);
-    if constexpr (TIN)
-      add_b2<NA>(fresh(tabs, toff), -0.5 * k * ie, [&](int i) { return (double)aG[i]; }, up, W);
-    solve(W, cp.hb * pO, 0.0, 0.0);
     if (zero_grp) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) W[i] = zero ? 0.0 : W[i];
     }
-    // U, in place of p: rows from the first, each after its last use
+    // U, in place of p (each row after its last use)
     {
-      double prev = fma(k, U[0], (double)aL[0]);
-      prev = up ? prev : 2.0 * prev;
-      double cur = fma(k, U[1], (double)aL[1]);
-      const Rows<NA> rows = fresh(tabs, toff);
-#pragma unroll
-      for (int i = 1; i < NA; ++i) {
-        const double next = i + 1 < NA ? fma(k, U[i + 1], (double)aL[i + 1]) : 0.0;
-        const double2 w = rows.t(i);
-        U[i] = -ie * fma(w.x, prev - cur, -(w.y * (cur - next)));
-        prev = cur;
-        cur = next;
-      }
+      const double fp = zero ? 0.0 : ik, fl = 0.25 * H;
+      add_b2<NA, true, true>(
+          fresh(tabs, toff), [&](int i) { return fma(fp, U[i], fl * (double)aL[i]); }, up, U);
+      if constexpr (TIN)
+        add_b<NA, false, false>(fresh(tabs, toff), [&](int i) { return aG[i]; }, up, xaddr, U);
+      solve(U, fl * pS, wU0, wUH);
     }
-    if constexpr (TIN) add_b<NA>(fresh(tabs, toff), 0.5 * ie, [&](int i) { return aG[i]; }, up, U);
-    solve(U, cp.hb * pS, wU0, wUH);
     // T
     if constexpr (sizeof(D) == 8) {
       forward(No{}, Yes{});
@@ -631,11 +693,14 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
         if constexpr (TIN) aH[i] = park[(NA + i) * 64];
       }
     }
-#pragma unroll
-    for (int i = 0; i < NA; ++i) Y[i] = 0.0;
-    add_b2<NA>(fresh(tabs, toff), -ie, [&](int i) { return (double)aT[i]; }, up, Y);
-    if constexpr (TIN) add_b<NA>(fresh(tabs, toff), -0.5 * ie, [&](int i) { return aH[i]; }, up, Y);
-    solve(Y, 0.0, wT0, wTH);
+    {
+      const double ft = 0.25 * H;
+      add_b2<NA, true, true>(fresh(tabs, toff), [&](int i) { return ft * (double)aT[i]; }, up,
+                             Y);
+      if constexpr (TIN)
+        add_b<NA, false, true>(fresh(tabs, toff), [&](int i) { return aH[i]; }, up, xaddr, Y);
+      solve(Y, 0.0, wT0, wTH);
+    }
 
     // --- wall correction -------------------------------------------------------------
     // adds the node functions E = e^{kap (z - z0)} and Z = z E, transformed in
@@ -686,7 +751,7 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
           const int i = j + h * kHalf;
           const double E = (double)(h ? e1 : e0), Z = (double)(h ? q1 : q0);
           U[i] = fma(E, eU, fma(Z, zU, U[i]));
-          W[i] = fma(E, eW, fma(Z, zW, W[i]));
+          W[i] = fma(E, cWU * eW, fma(Z, cWU * zW, W[i]));
           Y[i] = fma(E, eT, Y[i]);
         }
       }
@@ -697,13 +762,13 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
     wall_sums<NA>(W, up, tW, bW);
     wall_sums<NA>(Y, up, tT, bT);
     double U0 = wU0 - bU, T0 = wT0 - bT, UH = wUH - tU, TH = wTH - tT;
-    const double w0 = -bW, wH = -tW;
+    const double w0 = -cUW * bW, wH = -cUW * tW;    // (in the units of U)
     if (slip) {
       double dt, db;
-      wall_dsums<NA>(U, up, dt, db);
+      wall_dsums<NA>(fresh(tabs, toff), U, up, dt, db);
       U0 += l0 * s2H * db;
       UH -= lH * s2H * dt;
-      wall_dsums<NA>(Y, up, dt, db);
+      wall_dsums<NA>(fresh(tabs, toff), Y, up, dt, db);
       T0 += l0 * s2H * db;
       TH -= lH * s2H * dt;
     }
@@ -725,7 +790,10 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       // slip row at z = 0 gives g; what is left are two rows (w and i u_L at
       // z = H) for D_z~ and h.  Without slip their determinant is
       // 4 q^2 E^2 - s^2, taken without cancellation (q = kH, s = 1 - E^2).
-      const double q = kp * H, E = exp(-q), E2 = E * E, s = -expm1(-2.0 * q);
+      const double q = kp * H;
+      double E, s, ex;
+      wall_decay((LdsPtr)fact, q, E, s, ex);
+      const double E2 = E * E;
       const double r0 = i0 * (1.0 - 2.0 * p0);
       const double gam = q * (1.0 - pH) - (1.0 - 2.0 * pH);
       const double G0 = i0 * fma(1.0 + p0, w0, -U0);
@@ -735,7 +803,7 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       const double b1 = fma(-q * E, G0, fma(-E, w0, wH));
       const double b2 = fma(-E * gam, G0, fma(-E * (1.0 - pH), w0, UH));
       const double det = slip ? fma(a11, a22, -(a12 * a21))
-                              : -sinh_excess(q, E, s) * fma(2.0 * q, E, s);
+                              : -ex * fma(2.0 * q, E, s);
       const double id = frcp(det);
       double Dz = id * fma(b1, a22, -(b2 * a12)), h = id * fma(a11, b2, -(a21 * b1));
       double g = fma(-E * r0, h, fma(-2.0 * E * i0, Dz, G0));
@@ -747,7 +815,7 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       double DT = it * ((1.0 + p0) * TH - E * (1.0 - pH) * T0);
       if (zero) Dz = h = g = Cz = CT = DT = 0.0;
       const double CU = Cz - g, DU = -Dz - h, kg = kp * g, kh = kp * h;
-      if (kLow && low_grp) {
+      if constexpr (LOW) {
         // low-wavenumber square: node functions and transform in FP64 (their
         // combination cancels strongly as kH -> 0)
         basis(0.0, 0.0, -kp, kg, kg, CU, Cz, CT);
@@ -760,13 +828,15 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
 
     // --- inverse transform to the band nodes ---------------------------------------
     // vectors: U, W, T and, for the vorticity, (1/2)(k W + U') and -(1/2) T'
+    // (in the units of U)
     constexpr int kV = WOUT ? 5 : 3;
     D cf[kV][NA];
     if constexpr (WOUT) {
-      derivative<NA, D>(U, up, s2H, cf[3]);          // (1/2) (4/H) n a_n
-      derivative<NA, D>(Y, up, -s2H, cf[4]);
+      derivative<NA, D>(fresh(tabs, toff), U, up, xaddr, s2H, cf[3]);   // (1/2)(4/H)
+      derivative<NA, D>(fresh(tabs, toff), Y, up, xaddr, -s2H, cf[4]);
+      const double hw = 0.5 * k * cUW;
 #pragma unroll
-      for (int i = 0; i < NA; ++i) cf[3][i] += (D)(0.5 * k * W[i]);
+      for (int i = 0; i < NA; ++i) cf[3][i] += (D)(hw * W[i]);
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
@@ -778,9 +848,36 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
     for (int v = 0; v < kV; ++v)
 #pragma unroll
       for (int j = 0; j < kHalf; ++j) swap16(cf[v][j], cf[v][kHalf + j]);
-    const D sc = nyq ? D(0) : (D)cp.scale;
-    const D ox = (D)cx, oy = (D)cy, hk = (D)(0.5 * k);
-    for (int t = 0; lo + 16 * t <= hi; ++t) {
+    if (kAhead && grp + stride < last) {
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(w, grp + stride, s_lo, true, true);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const double su = cp.scale * cUW;               // (scale holds 1 / eta)
+    const D sw = (D)(su * cUW), ox = (D)(su * cx), oy = (D)(su * cy), hk = (D)(0.5 * k * su);
+    auto store = [&](int c, const D (&re)[kV], const D (&im)[kV]) {
+      if (c <= hi && valid) {
+        C* dst = out + (size_t)c * PS + idx;
+        auto put = [&](int ch, D r, D i) {
+          C o;
+          o.x = nyq ? T(0) : (T)r;
+          o.y = nyq ? T(0) : (T)i;
+          dst[(size_t)ch * N * PS] = o;
+        };
+        // u_L = -i U, omega_T = -i (i omega_T)
+        const D lr = im[0], li = -re[0], tr = re[2], ti = im[2];
+        put(0, fma(ox, lr, -(oy * tr)), fma(ox, li, -(oy * ti)));
+        put(1, fma(oy, lr, ox * tr), fma(oy, li, ox * ti));
+        put(2, sw * re[1], sw * im[1]);
+        if constexpr (WOUT) {
+          const D qr = im[3], qi = -re[3], pr = re[4], pim = im[4];
+          put(3, fma(ox, pr, -(oy * qr)), fma(ox, pim, -(oy * qi)));
+          put(4, fma(oy, pr, ox * qr), fma(oy, pim, ox * qi));
+          put(5, -hk * ti, hk * tr);
+        }
+      }
+    };
+    for (int t = 0; t < tiles; ++t) {
       Acc acc[kV][2];
 #pragma unroll
       for (int v = 0; v < kV; ++v) acc[v][0] = acc[v][1] = Acc{0, 0, 0, 0};
@@ -795,31 +892,58 @@ k_columns_mfma(ColParams cp, const int* __restrict__ band, const cplx_t<T>* in,
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int c = lo + 16 * t + M::row(g4, r);
-        if (c <= hi && valid) {
-          C* dst = out + (size_t)c * PS + idx;
-          auto put = [&](int ch, D re, D im) {
-            C o;
-            o.x = nyq ? T(0) : (T)(sc * re);
-            o.y = nyq ? T(0) : (T)(sc * im);
-            dst[(size_t)ch * N * PS] = o;
-          };
-          // u_L = -i U, omega_T = -i (i omega_T)
-          const D lr = acc[0][1][r], li = -acc[0][0][r];
-          const D tr = acc[2][0][r], ti = acc[2][1][r];
-          put(0, fma(ox, lr, -(oy * tr)), fma(ox, li, -(oy * ti)));
-          put(1, fma(oy, lr, ox * tr), fma(oy, li, ox * ti));
-          put(2, acc[1][0][r], acc[1][1][r]);
-          if constexpr (WOUT) {
-            const D qr = acc[3][1][r], qi = -acc[3][0][r];
-            const D pr = acc[4][0][r], pim = acc[4][1][r];
-            put(3, fma(ox, pr, -(oy * qr)), fma(ox, pim, -(oy * qi)));
-            put(4, fma(oy, pr, ox * qr), fma(oy, pim, ox * qi));
-            put(5, -hk * ti, hk * tr);
-          }
+        D re[kV], im[kV];
+#pragma unroll
+        for (int v = 0; v < kV; ++v) {
+          re[v] = acc[v][0][r];
+          im[v] = acc[v][1][r];
         }
+        store(lo + 16 * t + M::row(g4, r), re, im);
       }
     }
+    if constexpr (kTail) {
+      if (tail) {
+        // the last one to four nodes: sixteen 4 x 4 products of one
+        // coefficient each (a lane's block uses its own coefficients, a
+        // quarter of the series), then the four lane groups' sums are added so
+        // that group g keeps node g -- an eighth of the tile's matrix cycles
+        f4v acc[kV][2];
+#pragma unroll
+        for (int v = 0; v < kV; ++v) acc[v][0] = acc[v][1] = f4v{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j) {
+          const float a = pi[(tiles * kHalf + j) * 64 + ln];
+#pragma unroll
+          for (int v = 0; v < kV; ++v) {
+            acc[v][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, cf[v][j], acc[v][0], 0, 0, 0);
+            acc[v][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, cf[v][kHalf + j], acc[v][1],
+                                                           0, 0, 0);
+          }
+        }
+        auto gather = [&](const f4v& x) {
+          float a = x[0], b = x[1], c = x[2], d = x[3];
+          swap16(a, b);
+          swap16(c, d);
+          const float e = a + b, f = c + d;          // nodes 0, 1 and 2, 3
+          const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(e),
+                                                          __float_as_uint(f), false, false);
+          return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+        };
+        D re[kV], im[kV];
+#pragma unroll
+        for (int v = 0; v < kV; ++v) {
+          re[v] = gather(acc[v][0]);
+          im[v] = gather(acc[v][1]);
+        }
+        store(lo + 16 * tiles + g4, re, im);
+      }
+    }
+  }
+  };
+  if (kLow && (int)blockIdx.x < low_blocks) {
+    if constexpr (kLow) run(std::integral_constant<bool, true>{});
+  } else {
+    run(std::integral_constant<bool, false>{});
   }
 }
 
@@ -831,9 +955,13 @@ static void launch_one(const fcmdp_solver* s, const ColParams& cp, const void* i
   // as many workgroups as stay resident (registers: two per CU with FP32
   // transforms, one with FP64), each looping over column groups
   const int most = std::max(1, s->num_cu) * (sizeof(D) == 4 ? 2 : 1);
+  // one wavefront per group of the low-wavenumber columns: ns + 2 ranges of
+  // 2 ns + 1 columns
+  const int ns = s->dp.lowk_ns;
+  const int low = ns < 0 ? 0 : ((ns + 2) * (ns / 8 + 2) + 3) / 4;
   hipLaunchKernelGGL((k_columns_mfma<T, D, NT, NA, GEOM, TIN, WOUT>),
-                     dim3(std::min((G + 3) / 4, most)), dim3(256), 0, st, cp, s->band,
-                     (const C*)in, (C*)out, s->zc, s->dct_f, s->dct_i);
+                     dim3(std::min((G + 3) / 4, most) + low), dim3(256), 0, st, cp, low,
+                     s->band, (const C*)in, (C*)out, s->zc, s->dct_f, s->dct_i);
 }
 template <typename T, typename D, int NT, int NA, int GEOM>
 static void launch_channels(const fcmdp_solver* s, const ColParams& cp, const void* in,
@@ -855,13 +983,12 @@ hipError_t launch_columns_mfma(const fcmdp_solver* s, const void* spec_in,
                                void* spec_out, hipStream_t st) {
   ColParams cp;
   cp.dp = s->dp;
-  cp.scale = 1.0 / ((double)s->dp.Nx * (double)s->dp.Ny);
+  cp.scale = 1.0 / ((double)s->dp.Nx * (double)s->dp.Ny * s->dp.eta);
   cp.kxs = 2.0 * M_PI / s->dp.Lx;
   cp.kys = 2.0 * M_PI / s->dp.Ly;
   cp.dctf = s->dct_f;
-  cp.ie = 1.0 / s->dp.eta;
+  cp.iH = 1.0 / s->dp.H;
   cp.s2H = 2.0 / s->dp.H;
-  cp.hb = 0.25 * s->dp.H / s->dp.eta;
   // the smallest half-length that holds ceil(Nz / 2) coefficients per parity
   const int Nz = s->dp.Nz;
   if (s->mixed && Nz <= 32 && !s->force_vector_dct) {
