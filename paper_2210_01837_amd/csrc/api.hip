@@ -119,55 +119,6 @@ bool make_plan(int n, FFTPlan* plan) {
   return m == 1 && plan->nstages < fcmdp::kMaxStages;
 }
 
-// Plan for the row-owned transforms: radix 8 for the power-of-two part (one
-// 16, 4 or 2 for the remainder), then the odd primes.  Picks the fewest
-// threads per row (64, 128 or 256) for which every stage leaves at most
-// wave_nbi_cap(R) butterflies per thread; false if none does.
-bool make_wave_plan(int n, bool fp32, FFTPlan* plan, int* tpr) {
-  plan->n = n;
-  plan->nstages = 0;
-  int m = n, a = 0;
-  while (m % 2 == 0) { m /= 2; ++a; }
-  std::vector<int> r;
-  if (a % 3 == 1) {
-    if (a >= 4) { r.push_back(16); a -= 4; } else { r.push_back(2); a -= 1; }
-  } else if (a % 3 == 2) {
-    r.push_back(4);
-    a -= 2;
-  }
-  while (a >= 3) { r.push_back(8); a -= 3; }
-  const int primes[] = {3, 5, 7, 11, 13, 17};
-  for (int q : primes)
-    while (m % q == 0) { r.push_back(q); m /= q; }
-  if (m != 1 || (int)r.size() >= fcmdp::kMaxStages) return false;
-  for (int t = 64; t <= 256; t *= 2) {
-    bool ok = true;
-    for (int R : r)
-      if ((n / R + t - 1) / t > fcmdp::wave_nbi_cap(fp32, R)) ok = false;
-    if (ok) {
-      for (int R : r) plan->radix[plan->nstages++] = R;
-      *tpr = t;
-      return true;
-    }
-  }
-  return false;
-}
-
-// largest power of two <= maxrows with rows * row_bytes within the LDS budget
-int rows_fitting(size_t row_bytes, int maxrows) {
-  int r = maxrows;
-  while (r > 1 && (size_t)r * row_bytes > fcmdp::kLdsBudget) r /= 2;
-  return (size_t)r * row_bytes <= fcmdp::kLdsBudget ? r : 0;
-}
-
-// rows per workgroup of the x passes: the most (up to 16) that fit, and
-// twelve when sixteen do not fit but twelve do (1350-point rows): more
-// wavefronts and longer transposed runs than eight
-int default_rows_x(size_t row_bytes) {
-  const int r = rows_fitting(row_bytes, 16);
-  return r == 8 && 12 * row_bytes <= fcmdp::kLdsBudget ? 12 : r;
-}
-
 int validate(const fcmdp_params* p) {
   if (!p) return FCMDP_EINVAL;
   if (p->geometry != FCMDP_BOTTOM_WALL && p->geometry != FCMDP_SLIT_CHANNEL)
@@ -211,7 +162,7 @@ int validate(const fcmdp_params* p) {
   if (!make_plan(p->Nx / 2, &a) || !make_plan(p->Ny, &b)) return FCMDP_EINVAL;
   if ((long long)p->Nx * p->Ny >= (1LL << 31) - 1) return FCMDP_EINVAL;
   // LDS of the workgroup-per-row transforms (one row, two buffers), which
-  // every size must support; the wave-per-row transforms need less
+  // every size must support; the other transforms need less
   const size_t csz = p->precision == FCMDP_MIXED ? 8 : 16;
   if (2 * (size_t)p->Ny * csz > fcmdp::kLdsBudget) return FCMDP_EINVAL;
   if ((size_t)(p->Nx + 1) * csz > fcmdp::kLdsBudget) return FCMDP_EINVAL;
@@ -340,6 +291,24 @@ struct Uploader {
       const size_t j = ((size_t)m * s) % N;
       v[2 * m] = (T)root[2 * j];
       v[2 * m + 1] = (T)root[2 * j + 1];
+    }
+    to(dst, v);
+  }
+  // per-stage twiddles of a row plan, [q - 1][k] for stage s: e^{-2 pi i q k /
+  // (ns radix)}, from the roots of N = n step
+  template <typename T, typename P>
+  void stages(P** dst, const std::vector<double>& root, int step, const fcmdp::RowPlan& pl) {
+    std::vector<T> v(2 * (size_t)pl.ntw);
+    for (int s = 1; s < pl.nst; ++s) {
+      const int R = pl.radix[s], Ns = pl.ns[s];
+      const size_t unit = (size_t)step * (pl.n / (Ns * R));
+      for (int q = 1; q < R; ++q)
+        for (int k = 0; k < Ns; ++k) {
+          const size_t j = (size_t)q * k * unit;         // < N: q k < ns radix
+          const size_t e = 2 * ((size_t)pl.tw[s] + (size_t)(q - 1) * Ns + k);
+          v[e] = (T)root[2 * j];
+          v[e + 1] = (T)root[2 * j + 1];
+        }
     }
     to(dst, v);
   }
@@ -481,25 +450,10 @@ int fcmdp_create_solver(const fcmdp_params* p, void* hip_stream,
   }
   make_plan(p->Nx / 2, &s->plan_x);
   make_plan(p->Ny, &s->plan_y);
-  {
-    const bool fp32 = s->mixed;
-    const size_t csz = fp32 ? 8 : 16;
-    // row-owned transforms in single precision only (the double-precision
-    // stages do not fit the register budget of a 1024-thread workgroup)
-    s->wave_x = fp32 && make_wave_plan(p->Nx / 2, fp32, &s->wplan_x, &s->tpr_x);
-    s->wave_y = fp32 && make_wave_plan(p->Ny, fp32, &s->wplan_y, &s->tpr_y);
-    s->codelet_x = fcmdp::fft_codelet(p->Nx / 2, fp32, &s->wplan_x, &s->tpr_x);
-    s->codelet_y = fcmdp::fft_codelet(p->Ny, fp32, &s->wplan_y, &s->tpr_y);
-    if (s->codelet_x >= 0) s->wave_x = true;
-    if (s->codelet_y >= 0) s->wave_y = true;
-    const size_t row_x = (size_t)fcmdp::fft_lds_row(s->codelet_x, p->Nx / 2, true) * csz;
-    const size_t row_y = (size_t)fcmdp::fft_lds_row(s->codelet_y, p->Ny, false) * csz;
-    s->rows_x = default_rows_x(row_x);
-    // rows of the y pass are independent; one per workgroup packs LDS best
-    s->rows_y = s->codelet_y >= 0 ? 1 : rows_fitting(row_y, 8);
-    if (s->rows_x == 0) s->wave_x = false;
-    if (s->rows_y == 0) s->wave_y = false;
-  }
+  fcmdp::make_row_plan(p->Nx / 2, s->mixed, &s->rplan_x);
+  fcmdp::make_row_plan(p->Ny, s->mixed, &s->rplan_y);
+  s->codelet_x = fcmdp::fft_codelet(p->Nx / 2, s->mixed);
+  s->codelet_y = fcmdp::fft_codelet(p->Ny, s->mixed);
 
   // Workspace comes from the device's default memory pool in stream order.
   // Keep freed blocks in the pool (no release threshold), so that a solver
@@ -617,10 +571,14 @@ int fcmdp_create_solver(const fcmdp_params* p, void* hip_stream,
       upload.twiddles<float>(&s->tw_x, rx, 2, M);       // roots of Nx / 2
       upload.twiddles<float>(&s->tw_y, ry, 1, p->Ny);
       upload.twiddles<float>(&s->tw_r, rx, 1, M + 1);
+      upload.stages<float>(&s->tws_x, rx, 2, s->rplan_x);
+      upload.stages<float>(&s->tws_y, ry, 1, s->rplan_y);
     } else {
       upload.twiddles<double>(&s->tw_x, rx, 2, M);
       upload.twiddles<double>(&s->tw_y, ry, 1, p->Ny);
       upload.twiddles<double>(&s->tw_r, rx, 1, M + 1);
+      upload.stages<double>(&s->tws_x, rx, 2, s->rplan_x);
+      upload.stages<double>(&s->tws_y, ry, 1, s->rplan_y);
     }
   }
   if (err == FCMDP_OK) {
@@ -799,9 +757,8 @@ int fcmdp_set_variant(fcmdp_solver* s, int key, int value) {
           (size_t)fcmdp::fft_lds_row(x ? s->codelet_x : s->codelet_y,
                                      x ? s->p.Nx / 2 : s->p.Ny, x) * csz;
       const int maxr = x ? 16 : 8;   // capped at 1024 threads per workgroup
-      int r = value;
-      if (r == 0) r = x ? default_rows_x(row) : rows_fitting(row, maxr);
-      if (r < 1 || r > maxr || ((r & (r - 1)) && r != 12) ||
+      const int r = value;
+      if (r < 0 || r > maxr || ((r & (r - 1)) && r != 12) ||
           (size_t)r * row > fcmdp::kLdsBudget)
         return FCMDP_EINVAL;
       (x ? s->rows_x : s->rows_y) = r;
@@ -819,20 +776,10 @@ int fcmdp_set_variant(fcmdp_solver* s, int key, int value) {
     case FCMDP_VARIANT_VECTOR_DCT:
       s->force_vector_dct = on;
       return FCMDP_OK;
-    case FCMDP_VARIANT_NO_CODELET: {
-      const bool fp32 = s->mixed;
-      if (on) {
-        s->codelet_x = s->codelet_y = -1;
-        s->wave_x = fp32 && make_wave_plan(s->p.Nx / 2, fp32, &s->wplan_x, &s->tpr_x);
-        s->wave_y = fp32 && make_wave_plan(s->p.Ny, fp32, &s->wplan_y, &s->tpr_y);
-      } else {
-        s->codelet_x = fcmdp::fft_codelet(s->p.Nx / 2, fp32, &s->wplan_x, &s->tpr_x);
-        s->codelet_y = fcmdp::fft_codelet(s->p.Ny, fp32, &s->wplan_y, &s->tpr_y);
-        if (s->codelet_x >= 0) s->wave_x = true;
-        if (s->codelet_y >= 0) s->wave_y = true;
-      }
+    case FCMDP_VARIANT_NO_CODELET:
+      s->codelet_x = on ? -1 : fcmdp::fft_codelet(s->p.Nx / 2, s->mixed);
+      s->codelet_y = on ? -1 : fcmdp::fft_codelet(s->p.Ny, s->mixed);
       return FCMDP_OK;
-    }
     case FCMDP_VARIANT_NO_PIPELINE:
       s->force_no_pipeline = on;
       return FCMDP_OK;

@@ -49,13 +49,15 @@ struct FFTPlan {
   int radix[kMaxStages] = {0};
 };
 
-// The row-owned transforms hold all butterflies of one thread for a stage in
-// registers: at most wave_nbi_cap(R) butterflies of radix R per thread, so a
-// stage of length N needs ceil(N / (R * threads per row)) <= cap.
-__host__ __device__ constexpr int wave_nbi_cap(bool fp32, int R) {
-  return (fp32 ? 24 : 12) / R < 1 ? 1
-         : (fp32 ? 24 : 12) / R > 8 ? 8 : (fp32 ? 24 : 12) / R;
-}
+// Run-time plan of the row transforms in fft_rows.hip: radices, product of the
+// earlier ones, offsets of the stages' twiddles, and multipliers that replace
+// the divisions by ns and by n / radix.
+constexpr int kRowStages = 8;
+struct RowPlan {
+  int n = 0, nst = 0, ntw = 0;
+  int radix[kRowStages] = {0}, ns[kRowStages] = {0}, tw[kRowStages] = {0};
+  unsigned mns[kRowStages] = {0}, mnb[kRowStages] = {0};
+};
 
 // Parameters the device kernels need (passed by value).
 struct DevParams {
@@ -148,13 +150,14 @@ struct fcmdp_solver {
   void* tw_r = nullptr;         // e^{-2 pi i k/Nx}, k <= Nx/2
   fcmdp::FFTPlan plan_x, plan_y;
   int dft_off[32] = {0};        // offset of prime P's table in dftc
-  // row-owned transforms (x rows of Nx/2, y rows of Ny) when every stage
-  // fits the register budget with at most 256 threads per row; rows per
-  // workgroup and threads per row of each pass
-  fcmdp::FFTPlan wplan_x, wplan_y;
-  bool wave_x = false, wave_y = false;
-  int rows_x = 0, rows_y = 0, tpr_x = 0, tpr_y = 0;
-  int codelet_x = -1, codelet_y = -1;   // fixed-plan kernels, -1 = none
+  // row transforms of x (Nx/2 points) and y (Ny): fixed-plan kernels where the
+  // length has one (codelet index, -1 = none), else the run-time plans rplan_*
+  // with their per-stage twiddles; rows per workgroup (0 = default)
+  fcmdp::RowPlan rplan_x, rplan_y;
+  void* tws_x = nullptr;
+  void* tws_y = nullptr;
+  int rows_x = 0, rows_y = 0;
+  int codelet_x = -1, codelet_y = -1;
   void* dftc_t = nullptr;       // dftc converted to T
 
   // use the one-thread-per-column solver (tests)
@@ -233,13 +236,17 @@ hipError_t launch_fft_forward(const fcmdp_solver* s, const void* grid,
                               void* spec, hipStream_t st);
 hipError_t launch_fft_inverse(const fcmdp_solver* s, void* spec, void* grid,
                               hipStream_t st);
-// index of a fixed-plan kernel for length n (its plan and threads per row are
-// written to plan / tpr), or -1
-int fft_codelet(int n, bool fp32, FFTPlan* plan, int* tpr);
-// LDS elements per row of the row-owned transforms of length n (x: Nx/2,
-// with room for the Nyquist element; y: Ny) for fixed plan `codelet` (-1:
-// run-time plan)
+// index of a fixed-plan kernel for length n, or -1
+int fft_codelet(int n, bool fp32);
+// LDS elements per row of the transforms of length n (x: Nx/2, with room for
+// the Nyquist element; y: Ny) for fixed plan `codelet` (-1: run-time plan)
 int fft_lds_row(int codelet, int n, bool x);
+// fft_rows.hip: row transforms by run-time plans
+bool make_row_plan(int n, bool fp32, RowPlan* pl);
+bool row_plan_fits(const RowPlan& pl, bool fp32);
+hipError_t launch_rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+                         hipStream_t st);
+hipError_t launch_rows_y(const fcmdp_solver* s, void* spec, int sign, hipStream_t st);
 // columns.hip (one thread per column, a cross-check); columns_mfma.hip
 hipError_t launch_columns(const fcmdp_solver* s, const void* spec_in,
                           void* spec_out, hipStream_t st);

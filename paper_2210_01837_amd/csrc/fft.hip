@@ -13,124 +13,10 @@
 // and a split step with the twiddles e^{-2 pi i k/Nx}.  Only planes inside the
 // particle band [band[0], band[1]] are transformed.  All transforms are
 // unnormalised; the 1/(Nx Ny) factor is applied by the column solve.
+#include "dft.h"
 #include "fcmdp_internal.h"
 
 namespace fcmdp {
-
-template <typename C> __device__ inline C cmul(C a, C b) {
-  C r;
-  r.x = a.x * b.x - a.y * b.y;
-  r.y = a.x * b.y + a.y * b.x;
-  return r;
-}
-template <typename C> __device__ inline C cadd(C a, C b) {
-  C r; r.x = a.x + b.x; r.y = a.y + b.y; return r;
-}
-template <typename C> __device__ inline C csub(C a, C b) {
-  C r; r.x = a.x - b.x; r.y = a.y - b.y; return r;
-}
-// multiply by (sign * i)
-template <typename C, typename T> __device__ inline C cmul_si(C a, T sign) {
-  C r; r.x = -sign * a.y; r.y = sign * a.x; return r;
-}
-template <typename C, typename T> __device__ inline C cscale(C a, T s) {
-  C r; r.x = a.x * s; r.y = a.y * s; return r;
-}
-
-// ---- small DFTs: y_k = sum_q v_q e^{sign 2 pi i q k / R} --------------------
-template <typename T, typename C>
-__device__ inline void dft2(C* v) {
-  const C a = v[0], b = v[1];
-  v[0] = cadd(a, b);
-  v[1] = csub(a, b);
-}
-
-template <typename T, typename C>
-__device__ inline void dft4(C* v, T sign) {
-  const C s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-  const C s13 = cadd(v[1], v[3]), d13 = cmul_si<C, T>(csub(v[1], v[3]), sign);
-  v[0] = cadd(s02, s13);
-  v[2] = csub(s02, s13);
-  v[1] = cadd(d02, d13);
-  v[3] = csub(d02, d13);
-}
-
-template <typename T, typename C>
-__device__ inline void dft8(C* v, T sign) {
-  C e[4] = {v[0], v[2], v[4], v[6]};
-  C o[4] = {v[1], v[3], v[5], v[7]};
-  dft4<T, C>(e, sign);
-  dft4<T, C>(o, sign);
-  const T r = T(0.70710678118654752440084436210484903928);
-  C w1; w1.x = r; w1.y = sign * r;
-  C w3; w3.x = -r; w3.y = sign * r;
-  const C t0 = o[0];
-  const C t1 = cmul(o[1], w1);
-  const C t2 = cmul_si<C, T>(o[2], sign);
-  const C t3 = cmul(o[3], w3);
-  v[0] = cadd(e[0], t0); v[4] = csub(e[0], t0);
-  v[1] = cadd(e[1], t1); v[5] = csub(e[1], t1);
-  v[2] = cadd(e[2], t2); v[6] = csub(e[2], t2);
-  v[3] = cadd(e[3], t3); v[7] = csub(e[3], t3);
-}
-
-// radix 16 as two radix-8 halves (even / odd inputs) and one twiddled
-// radix-2 combination
-template <typename T, typename C>
-__device__ inline void dft16(C* v, T sign) {
-  C e[8], o[8];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) { e[m] = v[2 * m]; o[m] = v[2 * m + 1]; }
-  dft8<T, C>(e, sign);
-  dft8<T, C>(o, sign);
-  // cos and sin of pi k / 8, k = 0..7
-  const T c[8] = {T(1), T(0.92387953251128675613), T(0.70710678118654752440),
-                  T(0.38268343236508977173), T(0), T(-0.38268343236508977173),
-                  T(-0.70710678118654752440), T(-0.92387953251128675613)};
-  const T sn[8] = {T(0), T(0.38268343236508977173), T(0.70710678118654752440),
-                   T(0.92387953251128675613), T(1), T(0.92387953251128675613),
-                   T(0.70710678118654752440), T(0.38268343236508977173)};
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    C w; w.x = c[k]; w.y = sign * sn[k];
-    const C t = cmul(o[k], w);
-    v[k] = cadd(e[k], t);
-    v[k + 8] = csub(e[k], t);
-  }
-}
-
-// odd prime P: pair terms j and P-j; cs[2m], cs[2m+1] = cos, sin(2 pi m/P)
-template <typename T, typename C, int P>
-__device__ inline void dft_prime(C* v, const T* cs, T sign) {
-  constexpr int Hh = (P - 1) / 2;
-  C a[Hh], b[Hh];
-  C y0 = v[0];
-#pragma unroll
-  for (int j = 1; j <= Hh; ++j) {
-    a[j - 1] = cadd(v[j], v[P - j]);
-    b[j - 1] = csub(v[j], v[P - j]);
-    y0 = cadd(y0, a[j - 1]);
-  }
-  C out[P];
-  out[0] = y0;
-#pragma unroll
-  for (int k = 1; k <= Hh; ++k) {
-    C A = v[0];
-    C B; B.x = T(0); B.y = T(0);
-#pragma unroll
-    for (int j = 1; j <= Hh; ++j) {
-      const int m = (j * k) % P;
-      const T c = cs[2 * m], s = cs[2 * m + 1];
-      A.x += a[j - 1].x * c; A.y += a[j - 1].y * c;
-      B.x += b[j - 1].x * s; B.y += b[j - 1].y * s;
-    }
-    const C iB = cmul_si<C, T>(B, sign);
-    out[k] = cadd(A, iB);
-    out[P - k] = csub(A, iB);
-  }
-#pragma unroll
-  for (int k = 0; k < P; ++k) v[k] = out[k];
-}
 
 // One Stockham stage over nrows transforms of length N stored row-major.
 template <typename T, int R>
@@ -204,8 +90,6 @@ __device__ cplx_t<T>* fft_lds(cplx_t<T>* a, cplx_t<T>* b, int N,
   }
   return src;
 }
-
-struct DftOff { int off[32]; };
 
 // ---- x-pass, real -> half spectrum, transposed write -------------------------
 template <typename T>
@@ -331,102 +215,6 @@ __device__ __forceinline__ void row_sync() {
   if constexpr (TPR == 64) wave_sync();
   else __syncthreads();
 }
-
-// One Stockham stage of radix R on a row owned by TPR threads; each thread
-// holds up to NB butterflies in registers.  Rows are stored unpadded
-// (run-time plans).
-template <typename T, int R, int TPR, int NB>
-__device__ __forceinline__ void stage_body(cplx_t<T>* row, int N, int Ns, int t,
-                                           const cplx_t<T>* __restrict__ tw,
-                                           const T* __restrict__ cs, T sign) {
-  using C = cplx_t<T>;
-  const int nb = N / R;
-  const int twstep = N / (Ns * R);
-  C v[NB][R];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int j = t + TPR * i;
-    if (j < nb) {
-#pragma unroll
-      for (int q = 0; q < R; ++q) v[i][q] = row[j + q * nb];
-    }
-  }
-  row_sync<TPR>();
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int j = t + TPR * i;
-    if (j < nb) {
-      C* x = v[i];
-      const int k = j % Ns;
-      if (Ns > 1) {
-#pragma unroll
-        for (int q = 1; q < R; ++q) {
-          C w = tw[q * k * twstep];
-          w.y *= -sign;
-          x[q] = cmul(x[q], w);
-        }
-      }
-      if constexpr (R == 2) dft2<T, C>(x);
-      else if constexpr (R == 4) dft4<T, C>(x, sign);
-      else if constexpr (R == 8) dft8<T, C>(x, sign);
-      else if constexpr (R == 16) dft16<T, C>(x, sign);
-      else dft_prime<T, C, R>(x, cs, sign);
-      const int out = (j - k) * R + k;
-#pragma unroll
-      for (int q = 0; q < R; ++q) row[out + q * Ns] = x[q];
-    }
-  }
-  row_sync<TPR>();
-}
-
-// Generic plans: the radix is chosen at run time.  Not inlined: with every
-// radix inlined into one stage loop the register allocator keeps the union
-// of all stages' live ranges.
-template <typename T, int R, int TPR>
-__device__ __noinline__ void wstage(cplx_t<T>* row, int N, int Ns, int t,
-                                    const cplx_t<T>* __restrict__ tw,
-                                    const T* __restrict__ cs, T sign) {
-  stage_body<T, R, TPR, wave_nbi_cap(sizeof(T) == 4, R)>(row, N, Ns, t, tw, cs, sign);
-}
-
-template <typename T, int TPR>
-__device__ __forceinline__ void row_fft(cplx_t<T>* row, int N,
-                                        const FFTPlan& plan, int t,
-                                        const cplx_t<T>* __restrict__ tw,
-                                        const T* __restrict__ dftc,
-                                        const int* dft_off, T sign) {
-  int Ns = 1;
-  for (int s = 0; s < plan.nstages; ++s) {
-    const int R = plan.radix[s];
-    const T* cs = dftc + dft_off[R];
-    switch (R) {
-      case 2: wstage<T, 2, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 3: wstage<T, 3, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 4: wstage<T, 4, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 5: wstage<T, 5, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 7: wstage<T, 7, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 8: wstage<T, 8, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 11: wstage<T, 11, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 13: wstage<T, 13, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 16: wstage<T, 16, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      case 17: wstage<T, 17, TPR>(row, N, Ns, t, tw, cs, sign); break;
-      default: break;
-    }
-    Ns *= R;
-  }
-}
-
-struct GenericRows {
-  template <typename T, int TPR>
-  __device__ __forceinline__ static void run(cplx_t<T>* row, int N, const FFTPlan& plan, int t,
-                             const cplx_t<T>* __restrict__ tw,
-                             const T* __restrict__ dftc, const DftOff& doff,
-                             T sign) {
-    row_fft<T, TPR>(row, N, plan, t, tw, dftc, doff.off, sign);
-  }
-  // LDS elements a row of n occupies
-  __host__ __device__ static constexpr int span(int n) { return n; }
-};
 
 // ---- fixed plans ("codelets") ----------------------------------------------
 // The stage sequence is a template argument (stage code = 16 R + NB); stages
@@ -613,29 +401,6 @@ struct FixedRows {
 template <typename Run>
 __host__ __device__ constexpr int x_stride(int M) {
   return Run::span(M + 1) | 1;
-}
-
-// split step of the real transform: X_k from Z_k and Z_{M-k} (w = e^{-2 pi i k/Nx})
-template <typename C>
-__device__ inline C r2c_post(C zk, C zm, C w) {
-  using T = decltype(zk.x);
-  zm.y = -zm.y;
-  const C e = cscale(cadd(zk, zm), T(0.5));
-  const C d = csub(zk, zm);
-  C o; o.x = T(0.5) * d.y; o.y = T(-0.5) * d.x;      // -i d / 2
-  return cadd(e, cmul(w, o));
-}
-
-// inverse split step: Z_k from X_k and X_{M-k} (w = e^{-2 pi i k/Nx})
-template <typename C>
-__device__ inline C c2r_pre(C xk, C xm, C w) {
-  xm.y = -xm.y;                                   // conj(X_{M-k})
-  const C A = cadd(xk, xm);
-  const C B = csub(xk, xm);
-  w.y = -w.y;                                     // e^{+2 pi i k/Nx}
-  const C wb = cmul(w, B);
-  C z; z.x = A.x - wb.y; z.y = A.y + wb.x;        // A + i w B
-  return z;
 }
 
 // x-pass, real rows -> half spectrum, ROWS rows per workgroup, written
@@ -901,19 +666,31 @@ static void launch_wave_x(bool fwd, const fcmdp_solver* s, const void* in,
   const T* cs = (const T*)s->dftc_t;
   if (fwd)
     hipLaunchKernelGGL((k_fftw_x_r2c<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR),
-                       lds, st, dp, s->wplan_x, s->band, (const T*)in, (C*)out,
+                       lds, st, dp, s->plan_x, s->band, (const T*)in, (C*)out,
                        (const C*)s->tw_x, (const C*)s->tw_r, cs, doff);
   else
     hipLaunchKernelGGL((k_fftw_x_c2r<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR),
-                       lds, st, dp, s->wplan_x, s->band, (const C*)in, (T*)out,
+                       lds, st, dp, s->plan_x, s->band, (const C*)in, (T*)out,
                        (const C*)s->tw_x, (const C*)s->tw_r, cs, doff);
 }
 
+// rows per workgroup of the x passes: the most (up to 16) that fit in LDS, and
+// twelve when sixteen do not fit but twelve do (1350-point rows): more
+// wavefronts and longer transposed runs than eight
+static int rows_fitting(size_t row_bytes, int maxrows) {
+  int r = maxrows;
+  while (r > 1 && (size_t)r * row_bytes > kLdsBudget) r /= 2;
+  return r;
+}
 template <typename T, int TPR, typename Run>
 static void wave_x_rows(bool fwd, const fcmdp_solver* s, const void* in,
                         void* out, const DftOff& doff, hipStream_t st) {
-  // rows per workgroup, capped by 1024 threads
-  const int r = s->rows_x * TPR > 1024 ? 1024 / TPR : s->rows_x;
+  const size_t row = (size_t)x_stride<Run>(s->dp.Nx / 2) * sizeof(cplx_t<T>);
+  int r = s->rows_x;
+  if (r == 0) {
+    r = rows_fitting(row, 16);
+    if (r == 8 && 12 * row <= kLdsBudget) r = 12;
+  }
   switch (r) {
     case 16: launch_wave_x<T, 16, 64, Run>(fwd, s, in, out, doff, st); break;
     case 12: launch_wave_x<T, 12, 64, Run>(fwd, s, in, out, doff, st); break;
@@ -932,15 +709,15 @@ static void launch_wave_y(const fcmdp_solver* s, void* spec, const DftOff& doff,
   const size_t lds = (size_t)ROWS * Run::span(dp.Ny) * sizeof(C);
   dim3 g((dp.Nkx + ROWS - 1) / ROWS, (sign < 0 ? dp.nch_in : dp.nch_out) * dp.Nz);
   hipLaunchKernelGGL((k_fftw_y<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR), lds, st,
-                     dp, s->wplan_y, s->band, (C*)spec, (const C*)s->tw_y,
+                     dp, s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
                      (const T*)s->dftc_t, doff, sign);
 }
 
 template <typename T, int TPR, typename Run>
 static void wave_y_rows(const fcmdp_solver* s, void* spec, const DftOff& doff,
                         T sign, hipStream_t st) {
-  const int r = s->rows_y * TPR > 1024 ? 1024 / TPR : s->rows_y;
-  switch (r) {
+  // rows are independent; one per workgroup packs LDS best
+  switch (s->rows_y) {
     case 8: launch_wave_y<T, 8, TPR, Run>(s, spec, doff, sign, st); break;
     case 4: launch_wave_y<T, 4, TPR, Run>(s, spec, doff, sign, st); break;
     case 2: launch_wave_y<T, 2, TPR, Run>(s, spec, doff, sign, st); break;
@@ -959,25 +736,14 @@ static void wave_y_pipe(const fcmdp_solver* s, void* spec, const DftOff& doff,
   const int per_cu = (int)std::min<size_t>(8, kLdsBudget / lds);
   const int g = std::max(1, s->num_cu) * std::max(1, per_cu);
   hipLaunchKernelGGL((k_fftw_y_pipe<T, Run>), dim3(g), dim3(64), lds, st, dp,
-                     s->wplan_y, s->band, (C*)spec, (const C*)s->tw_y,
+                     s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
                      (const T*)s->dftc_t, doff, sign,
                      sign < 0 ? dp.nch_in : dp.nch_out);
 }
 
 // Codelets compiled for the transform lengths of the large workloads (single
-// precision, 64 threads per row).  codelet_table[i] must agree with the
-// FixedRows instance that wave_x / wave_y launch for index i.
-struct CodeletDesc { int n; int tpr; int nst; int code[6]; };
-static const CodeletDesc kCodelets[] = {
-    {1088, 64, 3, {8 * 16 + 3, 8 * 16 + 3, 17 * 16 + 1}},           // 2176 / 2
-    {2176, 64, 3, {16 * 16 + 3, 8 * 16 + 5, 17 * 16 + 2}},          // 2176
-    {384, 64, 3, {16 * 16 + 1, 8 * 16 + 1, 3 * 16 + 2}},            // 768 / 2
-    {768, 64, 4, {4 * 16 + 3, 8 * 16 + 2, 8 * 16 + 2, 3 * 16 + 4}},  // 768
-    {1350, 64, 6, {3 * 16 + 8, 3 * 16 + 8, 3 * 16 + 8, 5 * 16 + 5,    // 2700 / 2
-                   5 * 16 + 5, 2 * 16 + 11}},
-    {2700, 64, 6, {3 * 16 + 15, 3 * 16 + 15, 3 * 16 + 15, 5 * 16 + 9,  // 2700
-                   5 * 16 + 9, 4 * 16 + 11}},
-};
+// precision, 64 threads per row); Codelet<i> has length kCodeletLength[i].
+static const int kCodeletLength[] = {1088, 2176, 384, 768, 1350, 2700};
 using Codelet0 = FixedRows<8 * 16 + 3, 8 * 16 + 3, 17 * 16 + 1>;
 using Codelet1 = FixedRows<16 * 16 + 3, 8 * 16 + 5, 17 * 16 + 2>;
 using Codelet2 = FixedRows<16 * 16 + 1, 8 * 16 + 1, 3 * 16 + 2>;
@@ -1001,16 +767,11 @@ static void wave_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
     case 5: wave_x_rows<T, 64, Codelet5>(fwd, s, in, out, doff, st); return;
     default: break;
   }
-  switch (s->tpr_x) {
-    case 64: wave_x_rows<T, 64, GenericRows>(fwd, s, in, out, doff, st); break;
-    case 128: wave_x_rows<T, 128, GenericRows>(fwd, s, in, out, doff, st); break;
-    default: wave_x_rows<T, 256, GenericRows>(fwd, s, in, out, doff, st); break;
-  }
 }
 
 template <typename T>
 static void wave_y(const fcmdp_solver* s, void* spec, const DftOff& doff,
-                   T sign, hipStream_t st) {
+                         T sign, hipStream_t st) {
   if (!s->force_no_pipeline) {
     switch (s->codelet_y) {
       case 0: wave_y_pipe<T, Codelet0>(s, spec, doff, sign, st); return;
@@ -1031,11 +792,6 @@ static void wave_y(const fcmdp_solver* s, void* spec, const DftOff& doff,
     case 5: wave_y_rows<T, 64, Codelet5>(s, spec, doff, sign, st); return;
     default: break;
   }
-  switch (s->tpr_y) {
-    case 64: wave_y_rows<T, 64, GenericRows>(s, spec, doff, sign, st); break;
-    case 128: wave_y_rows<T, 128, GenericRows>(s, spec, doff, sign, st); break;
-    default: wave_y_rows<T, 256, GenericRows>(s, spec, doff, sign, st); break;
-  }
 }
 
 int fft_lds_row(int codelet, int n, bool x) {
@@ -1046,21 +802,14 @@ int fft_lds_row(int codelet, int n, bool x) {
     case 3: return x ? x_stride<Codelet3>(n) : Codelet3::span(n);
     case 4: return x ? x_stride<Codelet4>(n) : Codelet4::span(n);
     case 5: return x ? x_stride<Codelet5>(n) : Codelet5::span(n);
-    default: return x ? x_stride<GenericRows>(n) : GenericRows::span(n);
+    default: return x ? (n + 1) | 1 : n;
   }
 }
 
-int fft_codelet(int n, bool fp32, FFTPlan* plan, int* tpr) {
+int fft_codelet(int n, bool fp32) {
   if (!fp32) return -1;
-  for (int i = 0; i < (int)(sizeof(kCodelets) / sizeof(kCodelets[0])); ++i) {
-    const CodeletDesc& c = kCodelets[i];
-    if (c.n != n) continue;
-    plan->n = n;
-    plan->nstages = c.nst;
-    for (int k = 0; k < c.nst; ++k) plan->radix[k] = c.code[k] >> 4;
-    *tpr = c.tpr;
-    return i;
-  }
+  for (int i = 0; i < (int)(sizeof(kCodeletLength) / sizeof(int)); ++i)
+    if (kCodeletLength[i] == n) return i;
   return -1;
 }
 
@@ -1073,83 +822,85 @@ static int rows_for(int len, size_t elem, int bufs_extra, int maxrows) {
   return r;
 }
 
-template <typename T>
-static hipError_t fwd_impl(const fcmdp_solver* s, const T* grid, void* spec,
-                           hipStream_t st) {
-  using C = cplx_t<T>;
-  const DevParams& dp = s->dp;
+static DftOff dft_offsets(const fcmdp_solver* s) {
   DftOff doff;
   for (int i = 0; i < 32; ++i) doff.off[i] = s->dft_off[i];
-  const int M = dp.Nx / 2;
-  const int planes = dp.nch_in * dp.Nz;
-  constexpr bool kRowOwned = sizeof(T) == 4;       // single precision only
-  if (kRowOwned && s->wave_x && !s->force_generic_fft) {
-    if constexpr (kRowOwned) wave_x<T>(true, s, grid, spec, doff, st);
-  } else {
-    int rows = rows_for(M, sizeof(C), 0, 16);
-    if (rows > dp.Ny) rows = dp.Ny;
-    size_t lds = 2 * (size_t)rows * M * sizeof(C);
-    hipLaunchKernelGGL(k_fft_x_r2c<T>, dim3((dp.Ny + rows - 1) / rows, planes),
-                       dim3(256), lds, st, dp, s->plan_x, s->band, grid, (C*)spec,
-                       (const C*)s->tw_x, (const C*)s->tw_r, s->dftc, doff, rows);
-  }
-  if (kRowOwned && s->wave_y && !s->force_generic_fft) {
-    if constexpr (kRowOwned) wave_y<T>(s, spec, doff, T(-1), st);
-    return hipGetLastError();
-  }
-  int ry = rows_for(dp.Ny, sizeof(C), 0, 16);
-  if (ry > dp.Nkx) ry = dp.Nkx;
-  size_t lds = 2 * (size_t)ry * dp.Ny * sizeof(C);
-  hipLaunchKernelGGL(k_fft_y<T>, dim3((dp.Nkx + ry - 1) / ry, planes),
-                     dim3(256), lds, st, dp, s->plan_y, s->band, (C*)spec,
-                     (const C*)s->tw_y, s->dftc, doff, ry, T(-1));
-  return hipGetLastError();
+  return doff;
 }
 
+// Passes with workgroup-owned rows, two buffers and radices up to 8 (a
+// cross-check: variant FCMDP_VARIANT_GENERIC_FFT).
 template <typename T>
-static hipError_t inv_impl(const fcmdp_solver* s, void* spec, T* grid,
-                           hipStream_t st) {
+static void generic_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+                      const DftOff& doff, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
-  DftOff doff;
-  for (int i = 0; i < 32; ++i) doff.off[i] = s->dft_off[i];
   const int M = dp.Nx / 2;
-  const int planes = dp.nch_out * dp.Nz;
-  constexpr bool kRowOwned = sizeof(T) == 4;       // single precision only
-  if (kRowOwned && s->wave_y && !s->force_generic_fft) {
-    if constexpr (kRowOwned) wave_y<T>(s, spec, doff, T(1), st);
-  } else {
-    int ry = rows_for(dp.Ny, sizeof(C), 0, 16);
-    if (ry > dp.Nkx) ry = dp.Nkx;
-    size_t lds = 2 * (size_t)ry * dp.Ny * sizeof(C);
-    hipLaunchKernelGGL(k_fft_y<T>, dim3((dp.Nkx + ry - 1) / ry, planes),
-                       dim3(256), lds, st, dp, s->plan_y, s->band, (C*)spec,
-                       (const C*)s->tw_y, s->dftc, doff, ry, T(1));
-  }
-  if (kRowOwned && s->wave_x && !s->force_generic_fft) {
-    if constexpr (kRowOwned) wave_x<T>(false, s, spec, grid, doff, st);
-    return hipGetLastError();
-  }
-  int rows = rows_for(M, sizeof(C), 1, 16);
+  const int planes = (fwd ? dp.nch_in : dp.nch_out) * dp.Nz;
+  int rows = rows_for(M, sizeof(C), fwd ? 0 : 1, 16);
   if (rows > dp.Ny) rows = dp.Ny;
-  size_t lds = (size_t)rows * (2 * M + 1) * sizeof(C);
-  hipLaunchKernelGGL(k_fft_x_c2r<T>, dim3((dp.Ny + rows - 1) / rows, planes),
-                     dim3(256), lds, st, dp, s->plan_x, s->band, (const C*)spec,
-                     grid, (const C*)s->tw_x, (const C*)s->tw_r, s->dftc, doff,
-                     rows);
+  const dim3 g((dp.Ny + rows - 1) / rows, planes);
+  if (fwd)
+    hipLaunchKernelGGL(k_fft_x_r2c<T>, g, dim3(256), 2 * (size_t)rows * M * sizeof(C), st,
+                       dp, s->plan_x, s->band, (const T*)in, (C*)out, (const C*)s->tw_x,
+                       (const C*)s->tw_r, s->dftc, doff, rows);
+  else
+    hipLaunchKernelGGL(k_fft_x_c2r<T>, g, dim3(256),
+                       (size_t)rows * (2 * M + 1) * sizeof(C), st, dp, s->plan_x, s->band,
+                       (const C*)in, (T*)out, (const C*)s->tw_x, (const C*)s->tw_r, s->dftc,
+                       doff, rows);
+}
+template <typename T>
+static void generic_y(const fcmdp_solver* s, void* spec, const DftOff& doff, T sign,
+                      hipStream_t st) {
+  using C = cplx_t<T>;
+  const DevParams& dp = s->dp;
+  int rows = rows_for(dp.Ny, sizeof(C), 0, 16);
+  if (rows > dp.Nkx) rows = dp.Nkx;
+  const int planes = (sign < 0 ? dp.nch_in : dp.nch_out) * dp.Nz;
+  hipLaunchKernelGGL(k_fft_y<T>, dim3((dp.Nkx + rows - 1) / rows, planes), dim3(256),
+                     2 * (size_t)rows * dp.Ny * sizeof(C), st, dp, s->plan_y, s->band,
+                     (C*)spec, (const C*)s->tw_y, s->dftc, doff, rows, sign);
+}
+
+// One pass: the fixed plan of the length where there is one, else the run-time
+// plan of fft_rows.hip.
+static hipError_t x_pass(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+                         hipStream_t st) {
+  const DftOff doff = dft_offsets(s);
+  if (s->force_generic_fft) {
+    if (s->mixed) generic_x<float>(fwd, s, in, out, doff, st);
+    else generic_x<double>(fwd, s, in, out, doff, st);
+  } else if (s->codelet_x >= 0) {
+    wave_x<float>(fwd, s, in, out, doff, st);
+  } else {
+    return launch_rows_x(fwd, s, in, out, st);
+  }
+  return hipGetLastError();
+}
+static hipError_t y_pass(const fcmdp_solver* s, void* spec, int sign, hipStream_t st) {
+  const DftOff doff = dft_offsets(s);
+  if (s->force_generic_fft) {
+    if (s->mixed) generic_y<float>(s, spec, doff, (float)sign, st);
+    else generic_y<double>(s, spec, doff, (double)sign, st);
+  } else if (s->codelet_y >= 0) {
+    wave_y<float>(s, spec, doff, (float)sign, st);
+  } else {
+    return launch_rows_y(s, spec, sign, st);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_fft_forward(const fcmdp_solver* s, const void* grid,
                               void* spec, hipStream_t st) {
-  return s->mixed ? fwd_impl<float>(s, (const float*)grid, spec, st)
-                  : fwd_impl<double>(s, (const double*)grid, spec, st);
+  const hipError_t e = x_pass(true, s, grid, spec, st);
+  return e != hipSuccess ? e : y_pass(s, spec, -1, st);
 }
 
 hipError_t launch_fft_inverse(const fcmdp_solver* s, void* spec, void* grid,
                               hipStream_t st) {
-  return s->mixed ? inv_impl<float>(s, spec, (float*)grid, st)
-                  : inv_impl<double>(s, spec, (double*)grid, st);
+  const hipError_t e = y_pass(s, spec, 1, st);
+  return e != hipSuccess ? e : x_pass(false, s, spec, grid, st);
 }
 
 }  // namespace fcmdp
