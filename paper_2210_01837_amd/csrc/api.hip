@@ -671,8 +671,7 @@ static int check_particles(fcmdp_solver* s, int64_t n) {
 
 static int particle_front(fcmdp_solver* s, int n, const void* pos,
                           const void* F, const void* T, hipStream_t st) {
-  if (fcmdp::launch_prep(s, n, pos, st) != hipSuccess) return FCMDP_EHIP;
-  if (fcmdp::launch_sort(s, n, st) != hipSuccess) return FCMDP_EHIP;
+  if (fcmdp::launch_sort(s, n, pos, st) != hipSuccess) return FCMDP_EHIP;
   if (fcmdp::launch_records(s, n, pos, F, T, st) != hipSuccess)
     return FCMDP_EHIP;
   return FCMDP_OK;
@@ -686,8 +685,7 @@ int fcmdp_apply_mobility(fcmdp_solver* s, int64_t n, const void* pos,
   hipStream_t st = (hipStream_t)hip_stream;
   if (n > 0 && (!pos || !F || !U)) return FCMDP_EINVAL;
   if (n == 0) {
-    return fcmdp::launch_prep(s, 0, nullptr, st) == hipSuccess ? FCMDP_OK
-                                                               : FCMDP_EHIP;
+    return fcmdp::launch_sort(s, 0, nullptr, st) == hipSuccess ? FCMDP_OK : FCMDP_EHIP;
   }
   const int ni = (int)n;
   // without torques the grid and spectrum carry the three force channels;

@@ -199,9 +199,8 @@ namespace fcmdp {
 
 // --- launchers implemented in the .hip translation units -----------------
 // prep.hip
-hipError_t launch_prep(const fcmdp_solver* s, int n, const void* pos,
-                       hipStream_t st);
-hipError_t launch_sort(const fcmdp_solver* s, int n, hipStream_t st);
+// keys, band, domain errors, sort by cell, cell starts (n = 0: empty band only)
+hipError_t launch_sort(const fcmdp_solver* s, int n, const void* pos, hipStream_t st);
 hipError_t launch_records(const fcmdp_solver* s, int n, const void* pos,
                           const void* F, const void* T, hipStream_t st);
 hipError_t launch_set_band(const fcmdp_solver* s, int lo, int hi,

@@ -5,6 +5,8 @@
 // The sort makes every later reduction order a function of the input alone
 // (particles of one cell keep their input order), so spreading is
 // deterministic without atomics.
+#include <utility>
+
 #include "fcmdp_internal.h"
 #include "es.h"
 
@@ -13,43 +15,77 @@ namespace fcmdp {
 // ----------------------------------------------------------------------------
 // prep: keys, band, domain errors
 // ----------------------------------------------------------------------------
+constexpr int kSortThreads = 256;
+constexpr int kSortItems = 2048;                 // per workgroup and pass
+constexpr int kSortChunks = kSortItems / 64;     // 32
+// place of a digit's count of one workgroup: [workgroup][digit] or, for the
+// scan over workgroups, [digit][workgroup]
+struct HistAt {
+  int digit, block;
+  __device__ int operator()(int d, int b) const { return d * digit + b * block; }
+};
+
+// cell key of particle j (ncells if outside the domain) and its z window
+// (cB < cA: none)
 template <typename Tin>
-__global__ void __launch_bounds__(256)
+__device__ __forceinline__ uint32_t cell_key(const DevParams& dp, const double* zc,
+                                             const Tin* __restrict__ pos, int j, int* cA,
+                                             int* cB) {
+  const double x = (double)pos[3 * (size_t)j + 0];
+  const double y = (double)pos[3 * (size_t)j + 1];
+  const double z = (double)pos[3 * (size_t)j + 2];
+  *cA = 0;
+  *cB = -1;
+  bool ok = isfinite(x) && isfinite(y) && isfinite(z) && z >= 0.0;
+  if (ok) ok = dp.geometry == 0 ? (z + dp.alpha <= dp.H) : (z <= dp.H);
+  if (!ok) return (uint32_t)dp.ncells;
+  int ix, iy;
+  double fx, fy;
+  cell_of(wrap_coord(x, dp.Lx), dp.h, dp.Nx, &ix, &fx);
+  cell_of(wrap_coord(y, dp.Ly), dp.h, dp.Ny, &iy, &fy);
+  z_window(dp, zc, z, cA, cB);
+  return (uint32_t)(iy * dp.Nx + ix);
+}
+
+// keys, band and domain errors of 2048 particles per workgroup, and their
+// histogram of the first sort digit
+template <typename Tin>
+__global__ void __launch_bounds__(1024)
 k_prep(DevParams dp, int n, const Tin* __restrict__ pos,
        const double* __restrict__ zc, uint32_t* __restrict__ keys,
-       int* __restrict__ band, unsigned int* __restrict__ nbad) {
+       int* __restrict__ band, unsigned int* __restrict__ nbad, HistAt at,
+       uint32_t* __restrict__ hist) {
   __shared__ int s_lo, s_hi, s_bad;
+  __shared__ uint32_t h[256];
   if (threadIdx.x == 0) {
     s_lo = dp.Nz;
     s_hi = -1;
     s_bad = 0;
   }
+  if (threadIdx.x < 256) h[threadIdx.x] = 0;
   __syncthreads();
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) {
-    const double x = (double)pos[3 * (size_t)j + 0];
-    const double y = (double)pos[3 * (size_t)j + 1];
-    const double z = (double)pos[3 * (size_t)j + 2];
-    bool ok = isfinite(x) && isfinite(y) && isfinite(z) && z >= 0.0;
-    if (ok) ok = dp.geometry == 0 ? (z + dp.alpha <= dp.H) : (z <= dp.H);
-    if (!ok) {
-      keys[j] = (uint32_t)dp.ncells;
-      atomicAdd(&s_bad, 1);
-    } else {
-      int ix, iy;
-      double fx, fy;
-      cell_of(wrap_coord(x, dp.Lx), dp.h, dp.Nx, &ix, &fx);
-      cell_of(wrap_coord(y, dp.Ly), dp.h, dp.Ny, &iy, &fy);
-      keys[j] = (uint32_t)(iy * dp.Nx + ix);
-      int cA, cB;
-      z_window(dp, zc, z, &cA, &cB);
-      if (cB >= cA) {
-        atomicMin(&s_lo, cA);
-        atomicMax(&s_hi, cB);
-      }
+  int lo = dp.Nz, hi = -1, bad = 0;
+#pragma unroll
+  for (int i = 0; i < kSortItems / 1024; ++i) {
+    const int j = blockIdx.x * kSortItems + i * 1024 + threadIdx.x;
+    if (j >= n) break;
+    int cA, cB;
+    const uint32_t key = cell_key(dp, zc, pos, j, &cA, &cB);
+    keys[j] = key;
+    atomicAdd(&h[key & 255u], 1u);
+    if (key >= (uint32_t)dp.ncells) ++bad;
+    if (cB >= cA) {
+      lo = min(lo, cA);
+      hi = max(hi, cB);
     }
   }
+  if (hi >= 0) {
+    atomicMin(&s_lo, lo);
+    atomicMax(&s_hi, hi);
+  }
+  if (bad) atomicAdd(&s_bad, bad);
   __syncthreads();
+  if (threadIdx.x < 256) hist[at(threadIdx.x, blockIdx.x)] = h[threadIdx.x];
   if (threadIdx.x == 0) {
     // the band only widens, so a workgroup whose planes are already inside
     // it skips the (contended) atomics
@@ -68,21 +104,6 @@ __global__ void k_init_band(int* band, unsigned int* nbad, int lo, int hi,
   band[0] = lo;
   band[1] = hi;
   if (reset_bad) *nbad = 0u;
-}
-
-hipError_t launch_prep(const fcmdp_solver* s, int n, const void* pos,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(k_init_band, dim3(1), dim3(1), 0, st, s->band, s->nbad,
-                     s->dp.Nz, -1, 1);
-  if (n == 0) return hipGetLastError();
-  dim3 grid((n + 255) / 256);
-  if (s->mixed)
-    hipLaunchKernelGGL(k_prep<float>, grid, dim3(256), 0, st, s->dp, n,
-                       (const float*)pos, s->zc, s->keyA, s->band, s->nbad);
-  else
-    hipLaunchKernelGGL(k_prep<double>, grid, dim3(256), 0, st, s->dp, n,
-                       (const double*)pos, s->zc, s->keyA, s->band, s->nbad);
-  return hipGetLastError();
 }
 
 hipError_t launch_set_band(const fcmdp_solver* s, int lo, int hi,
@@ -117,18 +138,23 @@ hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t st) {
 }
 
 // ----------------------------------------------------------------------------
-// Stable LSD radix sort, 8-bit digits.  One block sorts 2048 consecutive
-// items per pass: 4 waves x 8 rounds x 64 lanes.  Stable ranks inside a
-// 64-item chunk come from eight ballots (lanes with an equal digit), chunk
-// counts are prefix-summed per digit in LDS, and block offsets come from a
-// digit-major exclusive scan of all block histograms.
+// Stable LSD radix sort, 8-bit digits.  Stable ranks inside a 64-item chunk
+// come from eight ballots (lanes with an equal digit), chunk counts are
+// prefix-summed per digit in LDS.
+//
+// Up to kSmallSort particles one workgroup does everything (keys, band and all
+// passes, with the items in LDS): the launches of the general path, about 4 us
+// each, were most of a small call's particle stage.  Beyond that a pass is a
+// histogram and a scatter of 2048 items per workgroup; a scatter workgroup
+// derives its offsets from the histograms itself while there are few of them
+// (kFewBlocks), otherwise a kernel scans each digit's counts first.  Figures at
+// launch_sort.
 // ----------------------------------------------------------------------------
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 2048;
-constexpr int kSortChunks = kSortItems / 64;   // 32
+constexpr int kSmallSort = 4096;
+constexpr int kFewBlocks = 64;
 
 __global__ void __launch_bounds__(kSortThreads)
-k_radix_hist(int n, const uint32_t* __restrict__ keys, int shift, int nblk,
+k_radix_hist(int n, const uint32_t* __restrict__ keys, int shift, HistAt at,
              uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
@@ -139,20 +165,67 @@ k_radix_hist(int n, const uint32_t* __restrict__ keys, int shift, int nblk,
     if (g < n) atomicAdd(&h[(keys[g] >> shift) & 255u], 1u);
   }
   __syncthreads();
-  hist[threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+  hist[at(threadIdx.x, blockIdx.x)] = h[threadIdx.x];
 }
 
+// exclusive prefix sum of one value per thread over the first 256 threads
+// (four wavefronts); every thread of the workgroup calls it
+__device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t* part) {
+  const int t = threadIdx.x, lane = t & 63;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (t < 256 && lane == 63) part[t >> 6] = x;
+  __syncthreads();
+  uint32_t base = 0;
+  for (int w = 0; w < (t >> 6) && w < 4; ++w) base += part[w];
+  return base + x - v;
+}
+
+// lanes of this wavefront with the same digit (among the active ones)
+__device__ __forceinline__ uint64_t same_digit(int d, bool active) {
+  uint64_t mask = __ballot(active);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint64_t bal = __ballot(((d >> b) & 1) != 0);
+    mask &= ((d >> b) & 1) ? bal : ~bal;
+  }
+  return mask;
+}
+
+// FEW: hist holds the workgroups' counts; else their exclusive sums per digit,
+// with the digits' totals in tot
+template <bool FEW>
 __global__ void __launch_bounds__(kSortThreads)
 k_radix_scatter(int n, const uint32_t* __restrict__ kin,
                 const int* __restrict__ vin, uint32_t* __restrict__ kout,
                 int* __restrict__ vout, int shift, int nblk,
-                const uint32_t* __restrict__ offs, int first_pass) {
+                const uint32_t* __restrict__ hist, const uint32_t* __restrict__ tot,
+                int first_pass) {
   __shared__ uint32_t cnt[kSortChunks][256];
   __shared__ uint32_t boff[256];
+  __shared__ uint32_t part[4];
   const int t = threadIdx.x;
   for (int i = t; i < kSortChunks * 256; i += kSortThreads)
     (&cnt[0][0])[i] = 0u;
-  boff[t] = offs[t * nblk + blockIdx.x];
+  {
+    uint32_t before = 0, total = 0;
+    if constexpr (FEW) {
+#pragma unroll 8
+      for (int b = 0; b < nblk; ++b) {
+        const uint32_t c = hist[b * 256 + t];
+        before += b < (int)blockIdx.x ? c : 0u;
+        total += c;
+      }
+    } else {
+      before = hist[(size_t)t * nblk + blockIdx.x];
+      total = tot[t];
+    }
+    boff[t] = before + scan256(total, part);
+  }
   __syncthreads();
 
   const int lane = t & 63;
@@ -171,12 +244,7 @@ k_radix_scatter(int n, const uint32_t* __restrict__ kin,
     uint32_t k = active ? kin[g] : 0u;
     int v = active ? (first_pass ? g : vin[g]) : 0;
     const int d = (int)((k >> shift) & 255u);
-    uint64_t mask = __ballot(active);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint64_t bal = __ballot(((d >> b) & 1) != 0);
-      mask &= ((d >> b) & 1) ? bal : ~bal;
-    }
+    const uint64_t mask = same_digit(d, active);
     key[r] = k;
     val[r] = v;
     dig[r] = active ? d : -1;
@@ -204,91 +272,227 @@ k_radix_scatter(int n, const uint32_t* __restrict__ kin,
   }
 }
 
-// Digit-major exclusive scan of the block histograms in two launches:
-// (1) block d scans the nblk counts of digit d and records the digit total;
-// (2) block d adds the totals of all smaller digits.
+// workgroup d: exclusive scan of digit d's counts over the workgroups, and
+// their total
 __global__ void __launch_bounds__(256)
 k_scan_digit(uint32_t* __restrict__ hist, int nblk, uint32_t* __restrict__ tot) {
-  __shared__ uint32_t part[256];
+  __shared__ uint32_t part[4], sum;
   uint32_t* a = hist + (size_t)blockIdx.x * nblk;
   const int t = threadIdx.x;
   uint32_t carry = 0;
   for (int base = 0; base < nblk; base += 256) {
     const int i = base + t;
     const uint32_t v = i < nblk ? a[i] : 0u;
-    part[t] = v;
+    const uint32_t x = scan256(v, part);
+    if (i < nblk) a[i] = carry + x;
+    if (t == 255) sum = x + v;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const uint32_t u = t >= off ? part[t - off] : 0u;
-      __syncthreads();
-      part[t] += u;
-      __syncthreads();
-    }
-    if (i < nblk) a[i] = carry + part[t] - v;
-    carry += part[255];
+    carry += sum;
     __syncthreads();
   }
   if (t == 0) tot[blockIdx.x] = carry;
 }
 
-__global__ void __launch_bounds__(256)
-k_scan_add(uint32_t* __restrict__ hist, int nblk, const uint32_t* __restrict__ tot) {
-  __shared__ uint32_t off;
-  if (threadIdx.x == 0) {
-    uint32_t s = 0;
-    for (int d = 0; d < (int)blockIdx.x; ++d) s += tot[d];
-    off = s;
+// keys, band, domain errors and the whole sort of n <= kSmallSort particles
+template <typename Tin>
+__global__ void __launch_bounds__(1024)
+k_small_sort(DevParams dp, int n, const Tin* __restrict__ pos, const double* __restrict__ zc,
+             uint32_t* __restrict__ keys, int* __restrict__ vals, int* __restrict__ band,
+             unsigned int* __restrict__ nbad, int passes) {
+  constexpr int kPer = kSmallSort / 1024, kChunks = kSmallSort / 64;
+  __shared__ uint32_t skey[kSmallSort];
+  __shared__ uint16_t sval[kSmallSort];
+  __shared__ uint16_t cnt[kChunks][256];
+  __shared__ uint32_t boff[256], part[4];
+  __shared__ int s_lo, s_hi, s_bad;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t == 0) {
+    s_lo = dp.Nz;
+    s_hi = -1;
+    s_bad = 0;
   }
   __syncthreads();
-  uint32_t* a = hist + (size_t)blockIdx.x * nblk;
-  for (int i = threadIdx.x; i < nblk; i += 256) a[i] += off;
+  // item q * 64 + lane of chunk q = 16 r + wave
+  const int chunks = (n + 63) / 64;
+  uint32_t key[kPer];
+  int val[kPer], lo = dp.Nz, hi = -1, bad = 0;
+#pragma unroll 1
+  for (int r = 0; r < kPer; ++r) {
+    const int g = (16 * r + wave) * 64 + lane;
+    if (16 * r >= chunks) break;                     // uniform
+    uint32_t k = 0xffffffffu;
+    if (g < n) {
+      int cA, cB;
+      k = cell_key(dp, zc, pos, g, &cA, &cB);
+      if (k >= (uint32_t)dp.ncells) ++bad;
+      if (cB >= cA) {
+        lo = min(lo, cA);
+        hi = max(hi, cB);
+      }
+    }
+    skey[g] = k;
+    sval[g] = (uint16_t)g;
+  }
+  if (hi >= 0) {
+    atomicMin(&s_lo, lo);
+    atomicMax(&s_hi, hi);
+  }
+  if (bad) atomicAdd(&s_bad, bad);
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  for (int pass = 0; pass < passes; ++pass) {
+    const int shift = 8 * pass;
+    for (int i = t; i < chunks * 128; i += 1024)
+      reinterpret_cast<uint32_t*>(&cnt[0][0])[i] = 0u;
+    __syncthreads();
+    int rank[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      if (16 * r >= chunks) break;                   // uniform
+      const int q = 16 * r + wave, g = q * 64 + lane;
+      const bool active = g < n;
+      key[r] = skey[g];
+      val[r] = sval[g];
+      const int d = (int)((key[r] >> shift) & 255u);
+      const uint64_t mask = same_digit(d, active);
+      rank[r] = __popcll(mask & lt_mask);
+      if (active && (mask & lt_mask) == 0ull) cnt[q][d] = (uint16_t)__popcll(mask);
+    }
+    __syncthreads();
+    uint32_t run = 0;
+    if (t < 256)
+      for (int q = 0; q < chunks; ++q) {
+        const uint32_t c = cnt[q][t];
+        cnt[q][t] = (uint16_t)run;
+        run += c;
+      }
+    const uint32_t off = scan256(run, part);
+    if (t < 256) boff[t] = off;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int q = 16 * r + wave, g = q * 64 + lane;
+      if (g < n) {
+        const int d = (int)((key[r] >> shift) & 255u);
+        const int dst = boff[d] + cnt[q][d] + rank[r];
+        skey[dst] = key[r];
+        sval[dst] = (uint16_t)val[r];
+      }
+    }
+    __syncthreads();
+  }
+  for (int g = t; g < n; g += 1024) {
+    keys[g] = skey[g];
+    vals[g] = sval[g];
+  }
+  if (t == 0) {
+    band[0] = s_lo;
+    band[1] = s_hi;
+    *nbad = (unsigned)s_bad;
+  }
 }
 
-// cell_start[c] = first sorted position with key >= c, for c = 0..ncells
-__global__ void k_cell_start(int n, int ncells, const uint32_t* __restrict__ keys,
-                             int* __restrict__ cell_start) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c > ncells) return;
-  int lo = 0, hi = n;
+// cell_start[c] = first sorted position with key >= c, for c = 0..ncells.  A
+// workgroup takes kCellBlock consecutive cells: half of its threads each find
+// the position of the first and of the past-the-end cell by a 128-ary search
+// over all keys (three rounds for two million; a binary search is a chain of
+// twenty dependent loads), then the threads search the keys between the two,
+// in LDS where they fit.
+constexpr int kCellBlock = 1024, kCellKeys = 2048;
+template <typename Keys>
+__device__ __forceinline__ int lower_bound(const Keys& keys, int lo, int hi, uint32_t c) {
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
-    if (keys[mid] < (uint32_t)c) lo = mid + 1; else hi = mid;
+    if (keys[mid] < c) lo = mid + 1; else hi = mid;
   }
-  cell_start[c] = lo;
+  return lo;
+}
+__global__ void __launch_bounds__(256)
+k_cell_start(int n, int ncells, const uint32_t* __restrict__ keys,
+             int* __restrict__ cell_start) {
+  __shared__ int cnt[2][2];
+  __shared__ uint32_t sk[kCellKeys];
+  const int c0 = blockIdx.x * kCellBlock;
+  const int side = threadIdx.x >> 7, t = threadIdx.x & 127;
+  const uint32_t c = (uint32_t)(c0 + side * kCellBlock);
+  int lo = 0, hi = n;                              // the answer is in [lo, hi]
+  while (true) {
+    const int len = hi - lo, step = len / 128 + 1;
+    // probes lo + step - 1, lo + 2 step - 1, ...: how many lie below c
+    const int p = lo + (t + 1) * step - 1;
+    const uint64_t below = __ballot(p < hi && keys[p < hi ? p : 0] < c);
+    if ((t & 63) == 0) cnt[side][t >> 6] = __popcll(below);
+    __syncthreads();
+    const int k = cnt[side][0] + cnt[side][1];
+    hi = min(hi, lo + (k + 1) * step - 1);
+    lo += k * step;
+    if (!__syncthreads_or(step > 1)) break;          // step 1: lo is the answer
+  }
+  if (t == 0) cnt[side][0] = lo;
+  __syncthreads();
+  lo = cnt[0][0];
+  hi = cnt[1][0];
+  const int m = hi - lo;
+  if (m <= kCellKeys) {
+    for (int i = threadIdx.x; i < m; i += 256) sk[i] = keys[lo + i];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < kCellBlock / 256; ++i) {
+    const int cell = c0 + i * 256 + threadIdx.x;
+    if (cell <= ncells)
+      cell_start[cell] = m <= kCellKeys ? lo + lower_bound(sk, 0, m, (uint32_t)cell)
+                                        : lower_bound(keys, lo, hi, (uint32_t)cell);
+  }
 }
 
-hipError_t launch_sort(const fcmdp_solver* s, int n, hipStream_t st) {
-  const int ncells = s->dp.ncells;
-  if (n > 0) {
+// Keys, band and domain errors of all particles, then the sort (keyA, valA) and
+// the cell starts.
+template <typename Tin>
+static void sort_impl(const fcmdp_solver* s, int n, const Tin* pos, hipStream_t st) {
+  if (n > 0 && n <= kSmallSort) {
+    hipLaunchKernelGGL(k_small_sort<Tin>, dim3(1), dim3(1024), 0, st, s->dp, n, pos, s->zc,
+                       s->keyA, s->valA, s->band, s->nbad, s->key_passes);
+  } else {
+    hipLaunchKernelGGL(k_init_band, dim3(1), dim3(1), 0, st, s->band, s->nbad, s->dp.Nz, -1,
+                       1);
+    if (n == 0) return;
     const int nblk = (n + kSortItems - 1) / kSortItems;
-    uint32_t* kin = s->keyA;
-    uint32_t* kout = s->keyB;
-    int* vin = s->valA;
-    int* vout = s->valB;
+    uint32_t* tot = s->hist + 256 * (size_t)s->nblk_cap;
+    // an odd number of passes starts in the second buffers, so that the
+    // result lies in keyA / valA
+    const bool odd = s->key_passes & 1;
+    uint32_t* kin = odd ? s->keyB : s->keyA;
+    uint32_t* kout = odd ? s->keyA : s->keyB;
+    int* vin = odd ? s->valB : s->valA;
+    int* vout = odd ? s->valA : s->valB;
+    const bool few = nblk <= kFewBlocks;
+    const HistAt at = few ? HistAt{1, 256} : HistAt{nblk, 1};
+    hipLaunchKernelGGL(k_prep<Tin>, dim3(nblk), dim3(1024), 0, st, s->dp, n, pos, s->zc, kin,
+                       s->band, s->nbad, at, s->hist);
     for (int pass = 0; pass < s->key_passes; ++pass) {
       const int shift = 8 * pass;
-      hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kSortThreads), 0, st,
-                         n, kin, shift, nblk, s->hist);
-      hipLaunchKernelGGL(k_scan_digit, dim3(256), dim3(256), 0, st, s->hist,
-                         nblk, s->hist + 256 * (size_t)s->nblk_cap);
-      hipLaunchKernelGGL(k_scan_add, dim3(256), dim3(256), 0, st, s->hist,
-                         nblk, s->hist + 256 * (size_t)s->nblk_cap);
-      hipLaunchKernelGGL(k_radix_scatter, dim3(nblk), dim3(kSortThreads), 0,
-                         st, n, kin, vin, kout, vout, shift, nblk, s->hist,
-                         pass == 0 ? 1 : 0);
-      uint32_t* tk = kin; kin = kout; kout = tk;
-      int* tv = vin; vin = vout; vout = tv;
-    }
-    // the result lives in keyA/valA when the pass count is even
-    if (kin != s->keyA) {
-      hipMemcpyAsync(s->keyA, kin, sizeof(uint32_t) * n,
-                     hipMemcpyDeviceToDevice, st);
-      hipMemcpyAsync(s->valA, vin, sizeof(int) * n, hipMemcpyDeviceToDevice,
-                     st);
+      if (pass > 0)
+        hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kSortThreads), 0, st, n, kin, shift,
+                           at, s->hist);
+      if (few) {
+        hipLaunchKernelGGL(k_radix_scatter<true>, dim3(nblk), dim3(kSortThreads), 0, st, n,
+                           kin, vin, kout, vout, shift, nblk, s->hist, tot, pass == 0);
+      } else {
+        hipLaunchKernelGGL(k_scan_digit, dim3(256), dim3(256), 0, st, s->hist, nblk, tot);
+        hipLaunchKernelGGL(k_radix_scatter<false>, dim3(nblk), dim3(kSortThreads), 0, st, n,
+                           kin, vin, kout, vout, shift, nblk, s->hist, tot, pass == 0);
+      }
+      std::swap(kin, kout);
+      std::swap(vin, vout);
     }
   }
-  hipLaunchKernelGGL(k_cell_start, dim3((ncells + 1 + 255) / 256), dim3(256),
-                     0, st, n, ncells, s->keyA, s->cell_start);
+  hipLaunchKernelGGL(k_cell_start, dim3(s->dp.ncells / kCellBlock + 1), dim3(256), 0, st, n,
+                     s->dp.ncells, s->keyA, s->cell_start);
+}
+
+hipError_t launch_sort(const fcmdp_solver* s, int n, const void* pos, hipStream_t st) {
+  if (s->mixed) sort_impl<float>(s, n, (const float*)pos, st);
+  else sort_impl<double>(s, n, (const double*)pos, st);
   return hipGetLastError();
 }
 
