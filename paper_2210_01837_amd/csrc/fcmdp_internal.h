@@ -220,6 +220,9 @@ hipError_t launch_interp(const fcmdp_solver* s, int n, const void* grid,
 bool interp_part_fits(const fcmdp_solver* s, int n);
 hipError_t launch_interp_part(const fcmdp_solver* s, int n, const void* grid,
                               void* U, void* Omega, hipStream_t st);
+// interp_wave.hip: one wavefront per particle
+hipError_t launch_interp_wave(const fcmdp_solver* s, int n, const void* grid, void* U,
+                              void* Omega, hipStream_t st);
 // lowk.hip: exact FP64 Chebyshev coefficients of the vertical force density
 // at the low wavenumbers (from the spread's f_z and fzlo planes)
 hipError_t launch_lowk(const fcmdp_solver* s, const void* grid, hipStream_t st);

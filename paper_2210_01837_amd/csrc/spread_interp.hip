@@ -568,7 +568,7 @@ hipError_t launch_spread(const fcmdp_solver* s, int n, void* grid, hipStream_t s
   if (!s->force_simple_spread) {
     // without torques only the three force channels are spread
     const bool dip = s->dp.nch_in == 6;
-    if (s->mixed && s->dp.lowk_ns < 0 && !s->force_wave_spread && spread_mfma_fits(s))
+    if (s->mixed && !s->force_wave_spread && spread_mfma_fits(s))
       return launch_spread_mfma(s, n, grid, st);
     if (s->mixed && s->dp.lowk_ns >= 0)
       dip ? spread_wave<float, 6, true>(s, grid, st)
@@ -995,9 +995,17 @@ static hipError_t interp_tiled(const fcmdp_solver* s, int n, const T* grid,
   return hipGetLastError();
 }
 
+// One wavefront per particle up to this many particles.  Measured at 0.45
+// particles per unit area and h = 1/1.731 (us, wavefront / aligned tiles): FP32
+// n = 1000 10 / 36, 4000 20 / 37, 8000 33 / 38, 16000 57 / 41, 131072 492 / 136;
+// FP64 1000 11 / 40, 4000 24 / 41, 8000 38 / 43, 16000 75 / 45.  The tiles cost
+// the same until there is more than one per CU; the wavefronts' cost grows with n.
+constexpr int kWaveInterp = 8192;
 hipError_t launch_interp(const fcmdp_solver* s, int n, const void* grid,
                          void* U, void* Omega, hipStream_t st) {
   if (n == 0) return hipSuccess;
+  if (!s->force_simple_interp && !s->force_halo_interp && n <= kWaveInterp)
+    return launch_interp_wave(s, n, grid, U, Omega, st);
   if ((!s->force_simple_interp || s->dp.dt_omega) && !s->force_halo_interp &&
       interp_part_fits(s, n))
     return launch_interp_part(s, n, grid, U, Omega, st);

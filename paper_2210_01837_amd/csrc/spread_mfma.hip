@@ -39,6 +39,7 @@ namespace fcmdp {
 namespace {
 
 typedef float sf4 __attribute__((ext_vector_type(4)));
+typedef double sd4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSZ = 20;          // planes per chunk
 constexpr int kSNB = 4;          // blocks of 16 slots per kernel
@@ -50,12 +51,17 @@ constexpr int kSW = 16;          // strip (and tile row) width in x
 // monopole z weights of the chunk [44, 64), 16-20 dipole z weights
 // [64, 84).  With torques through the kernel derivative (DT) also 21-25
 // the dipole's z-derivative weights [84, 104) and 26-29 its x/y derivative
-// weights [104, 120) (D' x, D' y; 8 each).  The LDS ring holds kCap
-// records (three workgroups per CU).
-template <bool DT> struct SRec {
-  static constexpr int kSlots = DT ? 32 : 24;
+// weights [104, 120) (D' x, D' y; 8 each).  With the vertical force in FP64
+// (FZ) the monopole z weights are the FP64 ones, pieces 11-20, and the dipole's
+// follow in 21-25 (both rows in FP32 beside them would leave two workgroups per
+// CU or a ring that the usual region and the next rows outgrow: 1.93 ms instead
+// of the figure below at sc1m).  The LDS ring holds kCap records (three workgroups per CU).
+template <bool DT, bool FZ> struct SRec {
+  static_assert(!(DT && FZ), "one use of the pieces from 11 on");
+  static constexpr int kSlots = DT ? 32 : FZ ? 26 : 24;
   static constexpr int kLen = 4 * kSlots;
   static constexpr int kCap = DT ? 96 : 128;
+  static constexpr int kZD = FZ ? 84 : 64;       // dipole z weights
   static constexpr int kZ = DT ? 3 : 2;          // z-weight rows
   static __device__ __forceinline__ int slot(int s) { return (unsigned)s % kCap; }
 };
@@ -104,14 +110,19 @@ __device__ __forceinline__ Roles lane_roles(int lane, int xb, int Nx) {
 // The B operand needs no zeroing: a particle that is out of range, or a
 // step slot past the end, has a zero A column, and every ring slot holds a
 // record (finite values), so its products vanish; slot 15 is never stored.
-template <int NCH, bool DT>
-__device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT>::kLen], int s0,
+// FZ: the vertical force once more in FP64 (FP32 weights in x and y, FP64 in
+// z), on two FP64 products with the operands exchanged: rows are planes
+// (z = c0 + 16 t + 4 r + lane / 16), columns the tile's columns, so that a
+// lane's stores join into 64-byte runs of one plane.
+template <int NCH, bool DT, bool FZ>
+__device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT, FZ>::kLen], int s0,
                                            int s1, int base, int y, const Roles& ro,
-                                           int Nx, int Ny, bool wrap, sf4 (&acc)[2][kSNB]) {
+                                           int Nx, int Ny, bool wrap, sf4 (&acc)[2][kSNB],
+                                           sd4 (&acc64)[2]) {
   for (int k0 = s0; k0 < s1; k0 += 4) {
     const int k = k0 + ro.g;
     const bool have = k < s1;
-    const float* rk = rec[SRec<DT>::slot(have ? k - base : 0)];
+    const float* rk = rec[SRec<DT, FZ>::slot(have ? k - base : 0)];
     const int ix = __float_as_int(rk[40]), iy = __float_as_int(rk[41]);
     int dx = ro.a - ix + 3;
     int dy = y - iy + 3;
@@ -152,12 +163,28 @@ __device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT>::kLen], i
         acc[0][bl] = __builtin_amdgcn_mfma_f32_16x16x4f32(avc, bc, acc[0][bl], 0, 0, 0);
       }
     } else {
+      if constexpr (FZ) {
+        const double wd = (double)rk[dxs] * (double)rk[8 + dys];
+        const double wv = ok ? wd : 0.0;
+        const double fz = (double)rk[34];
+        const double* p64 = reinterpret_cast<const double*>(rk + 44);
+        const bool in1 = ro.j < kSZ - 16;
+        const double z0 = fz * p64[ro.j], z1 = fz * p64[in1 ? 16 + ro.j : 16];
+        acc64[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(z0, wv, acc64[0], 0, 0, 0);
+        acc64[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(in1 ? z1 : 0.0, wv, acc64[1], 0, 0, 0);
+      }
 #pragma unroll
       for (int pt = 0; pt < (NCH == 6 ? 2 : 1); ++pt) {
         const float w = rk[16 * pt + dxs] * rk[16 * pt + 8 + dys];
         const float av = ok ? w : 0.f;
         const float f = rk[32 + 4 * pt + ro.ch];
-        const sf4 zw = *reinterpret_cast<const sf4*>(rk + 44 + kSZ * pt + 4 * ro.zg);
+        sf4 zw;
+        if (FZ && pt == 0) {
+          const double* p64 = reinterpret_cast<const double*>(rk + 44) + 4 * ro.zg;
+          zw = sf4{(float)p64[0], (float)p64[1], (float)p64[2], (float)p64[3]};
+        } else {
+          zw = *reinterpret_cast<const sf4*>(rk + (pt ? SRec<DT, FZ>::kZD : 44) + 4 * ro.zg);
+        }
 #pragma unroll
         for (int bl = 0; bl < kSNB; ++bl) {
           const float bv = f * zw[bl];
@@ -169,12 +196,30 @@ __device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT>::kLen], i
 }
 
 // Every band plane of the chunk of tile row y, zeros included.
-template <int NCH>
-__device__ __forceinline__ void tile_store(float* __restrict__ grid,
-                                           const sf4 (&acc)[2][kSNB], int c0, int lo,
+// FZ: f_z is the FP64 sum's FP32 value, its residual goes to fzlo.
+template <int NCH, bool FZ>
+__device__ __forceinline__ void tile_store(float* __restrict__ grid, float* __restrict__ fzlo,
+                                           const sf4 (&acc)[2][kSNB], const sd4 (&acc64)[2],
+                                           int c0, int lo,
                                            int hi, int y, const Roles& ro, int Nx,
                                            int Ny, size_t plane, size_t chstride,
                                            bool vst) {
+  if constexpr (FZ) {
+    if (y < Ny && ro.inside) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int dz = 16 * t + 4 * r + ro.g, z = c0 + dz;
+          if (dz >= kSZ || z < lo || z > hi) continue;
+          const size_t at = z * plane + (size_t)y * Nx + ro.a;
+          const double v = acc64[t][r];
+          const float h = (float)v;
+          grid[2 * chstride + at] = h;
+          fzlo[at] = (float)(v - (double)h);
+        }
+    }
+  }
   if (!ro.slot || y >= Ny || ro.xo >= Nx) return;
   const size_t col = (size_t)y * Nx + ro.xo;
 #pragma unroll
@@ -183,6 +228,7 @@ __device__ __forceinline__ void tile_store(float* __restrict__ grid,
     if (z < lo || z > hi) continue;
 #pragma unroll
     for (int pt = 0; pt < (NCH == 6 ? 2 : 1); ++pt) {
+      if (FZ && pt == 0 && ro.ch == 2) continue;
       const sf4 v = acc[pt][bl];
       float* dst = grid + (size_t)(ro.ch + 3 * pt) * chstride + z * plane + col;
       if (vst) {
@@ -204,15 +250,16 @@ __device__ __forceinline__ void wait_loads() {
 // NCH = 6: forces and torques; 3: forces only, or (DT) forces with the
 // torques through the derivative of the dipole kernel.  Blocks of BY rows
 // (8, or 16 for sparse particles: more work per staged row).
-template <int NCH, int BY, bool DT>
-__global__ void __launch_bounds__(256)
+template <int NCH, int BY, bool DT, bool FZ>
+__global__ void __launch_bounds__(256, FZ ? 3 : 1)
 k_spread_mfma(DevParams dp, const int* __restrict__ band,
               const int* __restrict__ cell_start, const int4* __restrict__ pinfo,
               const float* __restrict__ pw, const float* __restrict__ pf,
               const float* __restrict__ psi, const float* __restrict__ pdw,
-              const float* __restrict__ dpsi, float* __restrict__ grid, int nseg) {
+              const float* __restrict__ dpsi, const double* __restrict__ psi64,
+              float* __restrict__ grid, float* __restrict__ fzlo, int nseg) {
   static_assert(!DT || NCH == 3, "derivative torques spread three channels");
-  using R = SRec<DT>;
+  using R = SRec<DT, FZ>;
   constexpr int kSlots = R::kSlots, kSRec = R::kLen, kCap = R::kCap;
   constexpr int kBY = BY, kTPW = BY / 4;
   constexpr int kRows = BY + 6;            // cell rows of a block's region
@@ -264,6 +311,17 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
       } else if (part == 10) {
         pbase = reinterpret_cast<const char*>(pinfo); pstride = 16;
         pon = true;
+      } else if (FZ) {
+        // monopole z weights in FP64, dipole z weights
+        if (part < 21) {
+          const int z = c0 + 2 * (part - 11);
+          pbase = reinterpret_cast<const char*>(psi64 + (z < Nz ? z : Nz - 2));
+        } else {
+          const int z = c0 + 4 * (part - 21);
+          pbase = reinterpret_cast<const char*>(psi + Nz + (z < Nz ? z : Nz - 4));
+        }
+        pstride = 8u * Nz;
+        pon = vec && (NCH == 6 || part < 21);
       } else if (part < 11 + 5 * R::kZ) {
         // z weights: monopole, dipole, (DT) dipole derivative rows of the chunk
         const int u = part - 11, h = u / 5, uu = u - 5 * h;
@@ -298,8 +356,15 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
       } else {
         zbase = dpsi + zc; zstride = Nz;
       }
-      zon = !vec && lane < (NCH == 6 ? 2 : DT ? 3 : 1) * kSZ;
+      zon = !vec && lane < (NCH == 6 ? 2 : DT ? 3 : 1) * kSZ && !(FZ && lane < kSZ);
     }
+    // (FP64 weights: one word per lane)
+    const float* dbase = nullptr;
+    if constexpr (FZ) {
+      const int z = c0 + (lane >> 1);
+      dbase = reinterpret_cast<const float*>(psi64 + (z < Nz ? z : Nz - 1)) + (lane & 1);
+    }
+    const bool don = FZ && !vec && lane < 2 * kSZ;
     // stage particle p's record in ring slot s (s uniform)
     auto put = [&](int s, int p) {
       float* dst = rec[R::slot(s)];
@@ -309,8 +374,15 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
                                          16, 0, 0);
       if (zon)
         __builtin_amdgcn_global_load_lds(zbase + (size_t)p * zstride,
-                                         (__attribute__((address_space(3))) void*)(dst + 44),
+                                         (__attribute__((address_space(3))) void*)(
+                                             dst + R::kZD - kSZ),
                                          4, 0, 0);
+      if constexpr (FZ) {
+        if (don)
+          __builtin_amdgcn_global_load_lds(dbase + (size_t)p * 2 * Nz,
+                                           (__attribute__((address_space(3))) void*)(dst + 44),
+                                           4, 0, 0);
+      }
     };
 
     int S = 0;                 // stream index of the next staged particle
@@ -389,6 +461,7 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
             for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
               for (int q = 0; q < kSNB; ++q) acc[pt][q] = sf4{0.f, 0.f, 0.f, 0.f};
+            sd4 acc64[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
             for (int base = 0; base < tot; base += kCap) {
               const int cnt = tot - base < kCap ? tot - base : kCap;
               if (lane < 2 * kRows) {
@@ -402,12 +475,12 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
               wait_loads();
               __syncthreads();
               if (y < Ny)
-                tile_steps<NCH, DT>(rec, r0 > base ? r0 : base,
+                tile_steps<NCH, DT, FZ>(rec, r0 > base ? r0 : base,
                                     r1 < base + cnt ? r1 : base + cnt, base, y, ro, Nx,
-                                    Ny, true, acc);
+                                    Ny, true, acc, acc64);
               __syncthreads();             // the batch is read
             }
-            tile_store<NCH>(grid, acc, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
+            tile_store<NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
           }
           continue;                        // ring stays empty
         }
@@ -432,14 +505,15 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
         for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
           for (int q = 0; q < kSNB; ++q) acc[pt][q] = sf4{0.f, 0.f, 0.f, 0.f};
+        sd4 acc64[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
         const int y = yb + wv * kTPW + tt;
         if (y < Ny)
-          tile_steps<NCH, DT>(rec, rs[(y - 3) & 63], rs[(y + 4) & 63], 0, y, ro, Nx, Ny,
-                              seam, acc);
+          tile_steps<NCH, DT, FZ>(rec, rs[(y - 3) & 63], rs[(y + 4) & 63], 0, y, ro, Nx, Ny,
+                              seam, acc, acc64);
         // the next rows' loads were issued before the steps (and the first
         // tile row's stores one tile row ago): wait before the last stores
         if (tt == kTPW - 1) wait_loads();
-        tile_store<NCH>(grid, acc, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
+        tile_store<NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
       }
       __syncthreads();
       if (pend) {
@@ -468,7 +542,7 @@ bool spread_mfma_fits(const fcmdp_solver* s) {
   return s->dp.Nx >= kSW + 6 && s->dp.Ny >= 8 + 6;
 }
 
-template <int NCH, int BY, bool DT = false>
+template <int NCH, int BY, bool DT = false, bool FZ = false>
 static void spread_mfma_impl(const fcmdp_solver* s, void* grid, hipStream_t st) {
   const int gx = (s->dp.Nx + kSW - 1) / kSW, nby = (s->dp.Ny + BY - 1) / BY;
   const int nblk = gx * nby;
@@ -485,21 +559,22 @@ static void spread_mfma_impl(const fcmdp_solver* s, void* grid, hipStream_t st) 
     nwg = gx * nseg;
   }
   if (nwg > nblk) nwg = nblk;
-  hipLaunchKernelGGL((k_spread_mfma<NCH, BY, DT>), dim3(nwg), dim3(256), 0, st, s->dp,
+  hipLaunchKernelGGL((k_spread_mfma<NCH, BY, DT, FZ>), dim3(nwg), dim3(256), 0, st, s->dp,
                      s->band, s->cell_start, s->pinfo, (const float*)s->pw,
                      (const float*)s->pf, (const float*)s->psi,
                      DT ? (const float*)s->pdw : nullptr,
-                     DT ? (const float*)s->dpsi : nullptr, (float*)grid, nseg);
+                     DT ? (const float*)s->dpsi : nullptr, FZ ? s->psi64 : nullptr,
+                     (float*)grid, FZ ? s->fzlo : nullptr, nseg);
 }
 
 hipError_t launch_spread_mfma(const fcmdp_solver* s, int n, void* grid, hipStream_t st) {
   // 16-row blocks when a region and the next block's rows (22 x 38 cells)
   // hold about three quarters of the ring or fewer, so that the next rows
   // still load beside the current block
-  const bool dt = s->dp.dt_torque != 0;
+  const bool dt = s->dp.dt_torque != 0, fz = !dt && s->dp.lowk_ns >= 0;
   int by = s->spread_block_rows;
   if (by == 0) {
-    const double fill = 0.78 * (dt ? SRec<true>::kCap : SRec<false>::kCap);
+    const double fill = 0.78 * (dt ? SRec<true, false>::kCap : SRec<false, false>::kCap);
     by = (double)n * (22.0 * 38.0) <= fill * (double)s->dp.Nx * s->dp.Ny ? 16 : 8;
   }
   if (s->dp.Ny < 16 + 6) by = 8;
@@ -509,6 +584,16 @@ hipError_t launch_spread_mfma(const fcmdp_solver* s, int n, void* grid, hipStrea
     return hipGetLastError();
   }
   const bool dip = s->dp.nch_in == 6;
+  if (fz) {
+    // the slit channel's vertical force in FP64 (sc1m: 2.24 ms with the gather)
+    if (by == 16)
+      dip ? spread_mfma_impl<6, 16, false, true>(s, grid, st)
+          : spread_mfma_impl<3, 16, false, true>(s, grid, st);
+    else
+      dip ? spread_mfma_impl<6, 8, false, true>(s, grid, st)
+          : spread_mfma_impl<3, 8, false, true>(s, grid, st);
+    return hipGetLastError();
+  }
   if (by == 16)
     dip ? spread_mfma_impl<6, 16>(s, grid, st) : spread_mfma_impl<3, 16>(s, grid, st);
   else
