@@ -53,14 +53,16 @@ constexpr int kSW = 16;          // strip (and tile row) width in x
 // the dipole's z-derivative weights [84, 104) and 26-29 its x/y derivative
 // weights [104, 120) (D' x, D' y; 8 each).  With the vertical force in FP64
 // (FZ) the monopole z weights are the FP64 ones, pieces 11-20, and the dipole's
-// follow in 21-25 (both rows in FP32 beside them would leave two workgroups per
-// CU or a ring that the usual region and the next rows outgrow: 1.93 ms instead
-// of the figure below at sc1m).  The LDS ring holds kCap records (three workgroups per CU).
+// follow in 21-25 (with FP32 rows beside the FP64 ones, 31 pieces, a ring of 96
+// is outgrown by the usual region and the next rows: 1.93 ms at sc1m).  The LDS
+// ring holds kCap records, as many as leave three workgroups per CU (LDS is
+// given out in steps of 1280 bytes; a ring of 128 with FZ left two: 1.77 ms
+// against 1.26).
 template <bool DT, bool FZ> struct SRec {
   static_assert(!(DT && FZ), "one use of the pieces from 11 on");
   static constexpr int kSlots = DT ? 32 : FZ ? 26 : 24;
   static constexpr int kLen = 4 * kSlots;
-  static constexpr int kCap = DT ? 96 : 128;
+  static constexpr int kCap = DT ? 96 : FZ ? 124 : 128;
   static constexpr int kZD = FZ ? 84 : 64;       // dipole z weights
   static constexpr int kZ = DT ? 3 : 2;          // z-weight rows
   static __device__ __forceinline__ int slot(int s) { return (unsigned)s % kCap; }
