@@ -687,7 +687,14 @@ int fcmdp_apply_mobility(fcmdp_solver* s, int64_t n, const void* pos,
   if (n == 0) {
     return fcmdp::launch_sort(s, 0, nullptr, st) == hipSuccess ? FCMDP_OK : FCMDP_EHIP;
   }
-  const int ni = (int)n;
+  return fcmdp::apply_checked(s, (int)n, pos, F, T, U, Omega, st, false);
+}
+
+}  // extern "C"
+
+int fcmdp::apply_checked(fcmdp_solver* s, int ni, const void* pos, const void* F,
+                         const void* T, void* U, void* Omega, hipStream_t st,
+                         bool same_pos) {
   // without torques the grid and spectrum carry the three force channels;
   // without angular velocities the solve returns the three velocity channels.
   // Torques through the kernel derivative: three channels throughout, the
@@ -710,10 +717,11 @@ int fcmdp_apply_mobility(fcmdp_solver* s, int64_t n, const void* pos,
     if (prof) (void)hipEventRecord(ev[i], st);
   };
   mark(0);
-  v = particle_front(s, ni, pos, F, T, st);
+  const int v = same_pos ? (launch_forces(s, ni, F, st) == hipSuccess ? FCMDP_OK : FCMDP_EHIP)
+                         : particle_front(s, ni, pos, F, T, st);
   if (v != FCMDP_OK) return v;
   mark(1);
-  if (fcmdp::launch_spread(s, (int)n, s->grid, st) != hipSuccess) return FCMDP_EHIP;
+  if (fcmdp::launch_spread(s, ni, s->grid, st) != hipSuccess) return FCMDP_EHIP;
   mark(2);
   if (fcmdp::launch_fft_forward(s, s->grid, s->spec, st) != hipSuccess)
     return FCMDP_EHIP;
@@ -732,6 +740,8 @@ int fcmdp_apply_mobility(fcmdp_solver* s, int64_t n, const void* pos,
   if (prof) s->events.insert(s->events.end(), ev, ev + 7);
   return FCMDP_OK;
 }
+
+extern "C" {
 
 int fcmdp_set_profiling(fcmdp_solver* s, int enable) {
   if (!s) return FCMDP_EINVAL;

@@ -203,6 +203,8 @@ namespace fcmdp {
 hipError_t launch_sort(const fcmdp_solver* s, int n, const void* pos, hipStream_t st);
 hipError_t launch_records(const fcmdp_solver* s, int n, const void* pos,
                           const void* F, const void* T, hipStream_t st);
+// new forces in the records of the last launch_records
+hipError_t launch_forces(const fcmdp_solver* s, int n, const void* F, hipStream_t st);
 hipError_t launch_set_band(const fcmdp_solver* s, int lo, int hi,
                            hipStream_t st);
 hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t st);
@@ -223,6 +225,11 @@ hipError_t launch_interp_part(const fcmdp_solver* s, int n, const void* grid,
 // interp_wave.hip: one wavefront per particle
 hipError_t launch_interp_wave(const fcmdp_solver* s, int n, const void* grid, void* U,
                               void* Omega, hipStream_t st);
+// api.hip: the apply of fcmdp_apply_mobility on checked arguments; same_pos: the
+// sort and the records of the solver's last apply are of these positions and
+// channels, only the forces are new
+int apply_checked(fcmdp_solver* s, int n, const void* pos, const void* F, const void* T,
+                  void* U, void* Omega, hipStream_t st, bool same_pos);
 // lowk.hip: exact FP64 Chebyshev coefficients of the vertical force density
 // at the low wavenumbers (from the spread's f_z and fzlo planes)
 hipError_t launch_lowk(const fcmdp_solver* s, const void* grid, hipStream_t st);

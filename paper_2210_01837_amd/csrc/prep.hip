@@ -684,6 +684,28 @@ static void records_impl(const fcmdp_solver* s, int n, const void* pos,
                      (s->dp.dt_torque || s->dp.dt_omega) ? (T*)s->dpsi : nullptr);
 }
 
+// The forces of the records alone, for another apply on the same positions.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_forces(int n, int ncells, const uint32_t* __restrict__ skeys, const int* __restrict__ perm,
+         const T* __restrict__ F, T* __restrict__ pf) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n || skeys[i] >= (uint32_t)ncells) return;
+  const T* f = F + 3 * (size_t)perm[i];
+  store4(pf + 8 * (size_t)i, f[0], f[1], f[2], T(0));
+}
+
+hipError_t launch_forces(const fcmdp_solver* s, int n, const void* F, hipStream_t st) {
+  const dim3 g((n + 255) / 256);
+  if (s->mixed)
+    hipLaunchKernelGGL(k_forces<float>, g, dim3(256), 0, st, n, s->dp.ncells, s->keyA,
+                       s->valA, (const float*)F, (float*)s->pf);
+  else
+    hipLaunchKernelGGL(k_forces<double>, g, dim3(256), 0, st, n, s->dp.ncells, s->keyA,
+                       s->valA, (const double*)F, (double*)s->pf);
+  return hipGetLastError();
+}
+
 hipError_t launch_records(const fcmdp_solver* s, int n, const void* pos,
                           const void* F, const void* T, hipStream_t st) {
   if (n == 0) return hipSuccess;
