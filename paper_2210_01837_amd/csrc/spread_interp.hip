@@ -568,7 +568,7 @@ hipError_t launch_spread(const fcmdp_solver* s, int n, void* grid, hipStream_t s
   if (!s->force_simple_spread) {
     // without torques only the three force channels are spread
     const bool dip = s->dp.nch_in == 6;
-    if (s->mixed && !s->force_wave_spread && spread_mfma_fits(s))
+    if (!s->force_wave_spread && spread_mfma_fits(s))
       return launch_spread_mfma(s, n, grid, st);
     if (s->mixed && s->dp.lowk_ns >= 0)
       dip ? spread_wave<float, 6, true>(s, grid, st)

@@ -58,14 +58,37 @@ constexpr int kSW = 16;          // strip (and tile row) width in x
 // ring holds kCap records, as many as leave three workgroups per CU (LDS is
 // given out in steps of 1280 bytes; a ring of 128 with FZ left two: 1.77 ms
 // against 1.26).
-template <bool DT, bool FZ> struct SRec {
+template <typename T, bool DT, bool FZ> struct SRec {
   static_assert(!(DT && FZ), "one use of the pieces from 11 on");
   static constexpr int kSlots = DT ? 32 : FZ ? 26 : 24;
   static constexpr int kLen = 4 * kSlots;
   static constexpr int kCap = DT ? 96 : FZ ? 124 : 128;
-  static constexpr int kZD = FZ ? 84 : 64;       // dipole z weights
+  static constexpr int kZM = 44, kZD = FZ ? 84 : 64;   // monopole, dipole z weights
   static constexpr int kZ = DT ? 3 : 2;          // z-weight rows
   static __device__ __forceinline__ int slot(int s) { return (unsigned)s % kCap; }
+};
+// FP64 grid: the same record in doubles, 41 pieces (weights 0-15, forces and
+// torques 16-19, node base 20, z weights 21-30 and 31-40); two workgroups per CU.
+template <> struct SRec<double, false, false> {
+  static constexpr int kSlots = 41;
+  static constexpr int kLen = 2 * kSlots;
+  static constexpr int kCap = 123;
+  static constexpr int kZM = 42, kZD = 62, kZ = 2;
+  static __device__ __forceinline__ int slot(int s) { return (unsigned)s % kCap; }
+};
+
+template <typename T> struct SVec;
+template <> struct SVec<float> {
+  using type = sf4;
+  static __device__ __forceinline__ sf4 mma(float a, float b, sf4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct SVec<double> {
+  using type = sd4;
+  static __device__ __forceinline__ sd4 mma(double a, double b, sd4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
 };
 
 __device__ __forceinline__ int lane_value(int x, int l) {
@@ -89,11 +112,14 @@ struct Roles {
   bool inside, slot;
 };
 
+template <typename T>
 __device__ __forceinline__ Roles lane_roles(int lane, int xb, int Nx) {
   Roles r;
   r.g = lane >> 4;
   r.j = lane & 15;
-  r.a = xb + r.j;
+  // the FP64 product returns row 4 r + g in register r of group g: row 4 r + g
+  // stands for tile column 4 g + r, so that D has four neighbouring x either way
+  r.a = xb + (sizeof(T) == 4 ? r.j : 4 * (r.j & 3) + (r.j >> 2));
   r.inside = r.a < Nx;
   r.slot = r.j < 15;
   r.ch = r.j % 3;
@@ -116,16 +142,20 @@ __device__ __forceinline__ Roles lane_roles(int lane, int xb, int Nx) {
 // z), on two FP64 products with the operands exchanged: rows are planes
 // (z = c0 + 16 t + 4 r + lane / 16), columns the tile's columns, so that a
 // lane's stores join into 64-byte runs of one plane.
-template <int NCH, bool DT, bool FZ>
-__device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT, FZ>::kLen], int s0,
+template <typename T, int NCH, bool DT, bool FZ>
+__device__ __forceinline__ void tile_steps(const T (*rec)[SRec<T, DT, FZ>::kLen], int s0,
                                            int s1, int base, int y, const Roles& ro,
-                                           int Nx, int Ny, bool wrap, sf4 (&acc)[2][kSNB],
+                                           int Nx, int Ny, bool wrap,
+                                           typename SVec<T>::type (&acc)[2][kSNB],
                                            sd4 (&acc64)[2]) {
+  using R = SRec<T, DT, FZ>;
+  using V = typename SVec<T>::type;
   for (int k0 = s0; k0 < s1; k0 += 4) {
     const int k = k0 + ro.g;
     const bool have = k < s1;
-    const float* rk = rec[SRec<DT, FZ>::slot(have ? k - base : 0)];
-    const int ix = __float_as_int(rk[40]), iy = __float_as_int(rk[41]);
+    const T* rk = rec[R::slot(have ? k - base : 0)];
+    const int* node = reinterpret_cast<const int*>(rk + 40);
+    const int ix = node[0], iy = node[1];
     int dx = ro.a - ix + 3;
     int dy = y - iy + 3;
     if (wrap) {                    // wave-uniform
@@ -177,20 +207,23 @@ __device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT, FZ>::kLen
       }
 #pragma unroll
       for (int pt = 0; pt < (NCH == 6 ? 2 : 1); ++pt) {
-        const float w = rk[16 * pt + dxs] * rk[16 * pt + 8 + dys];
-        const float av = ok ? w : 0.f;
-        const float f = rk[32 + 4 * pt + ro.ch];
-        sf4 zw;
-        if (FZ && pt == 0) {
+        const T w = rk[16 * pt + dxs] * rk[16 * pt + 8 + dys];
+        const T av = ok ? w : T(0);
+        const T f = rk[32 + 4 * pt + ro.ch];
+        V zw;
+        if constexpr (sizeof(T) == 8) {
+          const T* zp = rk + (pt ? R::kZD : R::kZM) + 4 * ro.zg;
+          zw = V{zp[0], zp[1], zp[2], zp[3]};
+        } else if (FZ && pt == 0) {
           const double* p64 = reinterpret_cast<const double*>(rk + 44) + 4 * ro.zg;
           zw = sf4{(float)p64[0], (float)p64[1], (float)p64[2], (float)p64[3]};
         } else {
-          zw = *reinterpret_cast<const sf4*>(rk + (pt ? SRec<DT, FZ>::kZD : 44) + 4 * ro.zg);
+          zw = *reinterpret_cast<const sf4*>(rk + (pt ? R::kZD : R::kZM) + 4 * ro.zg);
         }
 #pragma unroll
         for (int bl = 0; bl < kSNB; ++bl) {
-          const float bv = f * zw[bl];
-          acc[pt][bl] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[pt][bl], 0, 0, 0);
+          const T bv = f * zw[bl];
+          acc[pt][bl] = SVec<T>::mma(av, bv, acc[pt][bl]);
         }
       }
     }
@@ -199,9 +232,10 @@ __device__ __forceinline__ void tile_steps(const float (*rec)[SRec<DT, FZ>::kLen
 
 // Every band plane of the chunk of tile row y, zeros included.
 // FZ: f_z is the FP64 sum's FP32 value, its residual goes to fzlo.
-template <int NCH, bool FZ>
-__device__ __forceinline__ void tile_store(float* __restrict__ grid, float* __restrict__ fzlo,
-                                           const sf4 (&acc)[2][kSNB], const sd4 (&acc64)[2],
+template <typename T, int NCH, bool FZ>
+__device__ __forceinline__ void tile_store(T* __restrict__ grid, float* __restrict__ fzlo,
+                                           const typename SVec<T>::type (&acc)[2][kSNB],
+                                           const sd4 (&acc64)[2],
                                            int c0, int lo,
                                            int hi, int y, const Roles& ro, int Nx,
                                            int Ny, size_t plane, size_t chstride,
@@ -231,10 +265,10 @@ __device__ __forceinline__ void tile_store(float* __restrict__ grid, float* __re
 #pragma unroll
     for (int pt = 0; pt < (NCH == 6 ? 2 : 1); ++pt) {
       if (FZ && pt == 0 && ro.ch == 2) continue;
-      const sf4 v = acc[pt][bl];
-      float* dst = grid + (size_t)(ro.ch + 3 * pt) * chstride + z * plane + col;
+      const typename SVec<T>::type v = acc[pt][bl];
+      T* dst = grid + (size_t)(ro.ch + 3 * pt) * chstride + z * plane + col;
       if (vst) {
-        *reinterpret_cast<sf4*>(dst) = v;
+        *reinterpret_cast<typename SVec<T>::type*>(dst) = v;
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -252,21 +286,23 @@ __device__ __forceinline__ void wait_loads() {
 // NCH = 6: forces and torques; 3: forces only, or (DT) forces with the
 // torques through the derivative of the dipole kernel.  Blocks of BY rows
 // (8, or 16 for sparse particles: more work per staged row).
-template <int NCH, int BY, bool DT, bool FZ>
-__global__ void __launch_bounds__(256, FZ ? 3 : 1)
+template <typename T, int NCH, int BY, bool DT, bool FZ>
+__global__ void __launch_bounds__(256, FZ ? 3 : sizeof(T) == 8 ? 2 : 1)
 k_spread_mfma(DevParams dp, const int* __restrict__ band,
               const int* __restrict__ cell_start, const int4* __restrict__ pinfo,
-              const float* __restrict__ pw, const float* __restrict__ pf,
-              const float* __restrict__ psi, const float* __restrict__ pdw,
-              const float* __restrict__ dpsi, const double* __restrict__ psi64,
-              float* __restrict__ grid, float* __restrict__ fzlo, int nseg) {
+              const T* __restrict__ pw, const T* __restrict__ pf,
+              const T* __restrict__ psi, const T* __restrict__ pdw,
+              const T* __restrict__ dpsi, const double* __restrict__ psi64,
+              T* __restrict__ grid, float* __restrict__ fzlo, int nseg) {
   static_assert(!DT || NCH == 3, "derivative torques spread three channels");
-  using R = SRec<DT, FZ>;
+  using R = SRec<T, DT, FZ>;
+  using V = typename SVec<T>::type;
+  constexpr bool kF64 = sizeof(T) == 8;
   constexpr int kSlots = R::kSlots, kSRec = R::kLen, kCap = R::kCap;
   constexpr int kBY = BY, kTPW = BY / 4;
   constexpr int kRows = BY + 6;            // cell rows of a block's region
   static_assert(2 * kRows <= 64 && 2 * BY + 7 <= 64, "lanes per segment, rows in rs");
-  __shared__ __align__(16) float rec[kCap][kSRec];
+  __shared__ __align__(16) T rec[kCap][kSRec];
   __shared__ int rs[64];      // stream index of the first particle of row r (r mod 64)
   __shared__ int pidx[kCap];  // batched staging: batch index -> particle
   const int tid = threadIdx.x, lane = tid & 63;
@@ -294,17 +330,34 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
   const int lo = band[0], hi = band[1];
   const size_t plane = (size_t)Nx * Ny;
   const size_t chstride = plane * Nz;
-  const bool vec = (Nz & 3) == 0;          // 16-byte aligned z-weight rows
-  const bool vst = (Nx & 3) == 0;          // 16-byte aligned grid rows
+  // 16-byte aligned z-weight rows and grid rows (of four elements)
+  const bool vec = kF64 ? (Nz & 1) == 0 : (Nz & 3) == 0;
+  const bool vst = (Nx & 3) == 0;
 
-  for (int c0 = vec ? (lo & ~3) : lo; c0 <= hi; c0 += kSZ) {
+  for (int c0 = vec ? (lo & (kF64 ? ~1 : ~3)) : lo; c0 <= hi; c0 += kSZ) {
     // piece `lane` of a record (lanes < kSlots): source and bytes per particle
     const char* pbase;
     unsigned pstride;
     bool pon;
     {
       const int part = lane < kSlots ? lane : kSlots - 1;
-      if (part < 8) {
+      if constexpr (kF64) {
+        if (part < 16) {
+          pbase = reinterpret_cast<const char*>(pw + 2 * part); pstride = 256;
+          pon = NCH == 6 || part < 8;
+        } else if (part < 20) {
+          pbase = reinterpret_cast<const char*>(pf + 2 * (part - 16)); pstride = 64;
+          pon = NCH == 6 || part < 18;
+        } else if (part == 20) {
+          pbase = reinterpret_cast<const char*>(pinfo); pstride = 16;
+          pon = true;
+        } else {
+          const int h = part < 31 ? 0 : 1, z = c0 + 2 * (part - 21 - 10 * h);
+          pbase = reinterpret_cast<const char*>(psi + h * Nz + (z < Nz ? z : Nz - 2));
+          pstride = 16u * Nz;                    // past Nz: never stored
+          pon = vec && (NCH == 6 || h == 0);
+        }
+      } else if (part < 8) {
         pbase = reinterpret_cast<const char*>(pw + 4 * part); pstride = 128;
         pon = NCH == 6 || DT || part < 4;
       } else if (part < 10) {
@@ -347,7 +400,7 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
     }
     // z-weight rows that are not 16-byte aligned: one float per lane
     // (lanes < 20 per row: monopole, dipole, dipole derivative)
-    const float* zbase;
+    const T* zbase;
     unsigned zstride;
     bool zon;
     {
@@ -358,18 +411,21 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
       } else {
         zbase = dpsi + zc; zstride = Nz;
       }
-      zon = !vec && lane < (NCH == 6 ? 2 : DT ? 3 : 1) * kSZ && !(FZ && lane < kSZ);
+      zon = !kF64 && !vec && lane < (NCH == 6 ? 2 : DT ? 3 : 1) * kSZ && !(FZ && lane < kSZ);
     }
     // (FP64 weights: one word per lane)
     const float* dbase = nullptr;
-    if constexpr (FZ) {
+    if constexpr (FZ || kF64) {
+      const double* row;
+      if constexpr (FZ) row = psi64;
+      else row = psi;
       const int z = c0 + (lane >> 1);
-      dbase = reinterpret_cast<const float*>(psi64 + (z < Nz ? z : Nz - 1)) + (lane & 1);
+      dbase = reinterpret_cast<const float*>(row + (z < Nz ? z : Nz - 1)) + (lane & 1);
     }
-    const bool don = FZ && !vec && lane < 2 * kSZ;
+    const bool don = (FZ || kF64) && !vec && lane < 2 * kSZ;
     // stage particle p's record in ring slot s (s uniform)
     auto put = [&](int s, int p) {
-      float* dst = rec[R::slot(s)];
+      T* dst = rec[R::slot(s)];
       if (pon)
         __builtin_amdgcn_global_load_lds(pbase + (size_t)p * pstride,
                                          (__attribute__((address_space(3))) void*)dst,
@@ -379,6 +435,19 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
                                          (__attribute__((address_space(3))) void*)(
                                              dst + R::kZD - kSZ),
                                          4, 0, 0);
+      if constexpr (kF64) {
+        if (don) {
+          __builtin_amdgcn_global_load_lds(dbase + (size_t)p * 4 * Nz,
+                                           (__attribute__((address_space(3))) void*)(
+                                               dst + R::kZM),
+                                           4, 0, 0);
+          if (NCH == 6)
+            __builtin_amdgcn_global_load_lds(dbase + (size_t)p * 4 * Nz + 2 * Nz,
+                                             (__attribute__((address_space(3))) void*)(
+                                                 dst + R::kZD),
+                                             4, 0, 0);
+        }
+      }
       if constexpr (FZ) {
         if (don)
           __builtin_amdgcn_global_load_lds(dbase + (size_t)p * 2 * Nz,
@@ -396,7 +465,7 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
       const int xb = sx * kSW, yb = by * kBY;
       if (sx != cur_sx) ring = false;      // a new strip: start over
       cur_sx = sx;
-      const Roles ro = lane_roles(lane, xb, Nx);
+      const Roles ro = lane_roles<T>(lane, xb, Nx);
       // the block's particle region (cells xb - 3 .. xb + 18, rows yb - 3 ..
       // yb + kBY + 2) crosses a periodic seam
       const bool seam = xb < 3 || xb + kSW + 3 > Nx || yb < 3 || yb + kBY + 3 > Ny;
@@ -458,11 +527,11 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
             const int t = wv * kTPW + tt;
             const int y = yb + t;
             const int r0 = lane_value(excl, 2 * t), r1 = lane_value(excl, 2 * (t + 7));
-            sf4 acc[2][kSNB];
+            V acc[2][kSNB];
 #pragma unroll
             for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
-              for (int q = 0; q < kSNB; ++q) acc[pt][q] = sf4{0.f, 0.f, 0.f, 0.f};
+              for (int q = 0; q < kSNB; ++q) acc[pt][q] = V{0, 0, 0, 0};
             sd4 acc64[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
             for (int base = 0; base < tot; base += kCap) {
               const int cnt = tot - base < kCap ? tot - base : kCap;
@@ -477,12 +546,12 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
               wait_loads();
               __syncthreads();
               if (y < Ny)
-                tile_steps<NCH, DT, FZ>(rec, r0 > base ? r0 : base,
+                tile_steps<T, NCH, DT, FZ>(rec, r0 > base ? r0 : base,
                                     r1 < base + cnt ? r1 : base + cnt, base, y, ro, Nx,
                                     Ny, true, acc, acc64);
               __syncthreads();             // the batch is read
             }
-            tile_store<NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
+            tile_store<T, NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
           }
           continue;                        // ring stays empty
         }
@@ -502,20 +571,20 @@ k_spread_mfma(DevParams dp, const int* __restrict__ band,
       }
 #pragma unroll
       for (int tt = 0; tt < kTPW; ++tt) {
-        sf4 acc[2][kSNB];
+        V acc[2][kSNB];
 #pragma unroll
         for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
-          for (int q = 0; q < kSNB; ++q) acc[pt][q] = sf4{0.f, 0.f, 0.f, 0.f};
+          for (int q = 0; q < kSNB; ++q) acc[pt][q] = V{0, 0, 0, 0};
         sd4 acc64[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
         const int y = yb + wv * kTPW + tt;
         if (y < Ny)
-          tile_steps<NCH, DT, FZ>(rec, rs[(y - 3) & 63], rs[(y + 4) & 63], 0, y, ro, Nx, Ny,
+          tile_steps<T, NCH, DT, FZ>(rec, rs[(y - 3) & 63], rs[(y + 4) & 63], 0, y, ro, Nx, Ny,
                               seam, acc, acc64);
         // the next rows' loads were issued before the steps (and the first
         // tile row's stores one tile row ago): wait before the last stores
         if (tt == kTPW - 1) wait_loads();
-        tile_store<NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
+        tile_store<T, NCH, FZ>(grid, fzlo, acc, acc64, c0, lo, hi, y, ro, Nx, Ny, plane, chstride, vst);
       }
       __syncthreads();
       if (pend) {
@@ -544,15 +613,15 @@ bool spread_mfma_fits(const fcmdp_solver* s) {
   return s->dp.Nx >= kSW + 6 && s->dp.Ny >= 8 + 6;
 }
 
-template <int NCH, int BY, bool DT = false, bool FZ = false>
+template <typename T, int NCH, int BY, bool DT = false, bool FZ = false>
 static void spread_mfma_impl(const fcmdp_solver* s, void* grid, hipStream_t st) {
   const int gx = (s->dp.Nx + kSW - 1) / kSW, nby = (s->dp.Ny + BY - 1) / BY;
   const int nblk = gx * nby;
   const int cus = s->num_cu > 0 ? s->num_cu : 256;
-  int nwg = s->spread_workgroups > 0 ? s->spread_workgroups : 3 * cus;
+  int nwg = s->spread_workgroups > 0 ? s->spread_workgroups : (sizeof(T) == 8 ? 2 : 3) * cus;
   // strips side by side when grid rows are not whole 128-byte lines (and
   // when asked); the segments per strip then keep every workgroup resident
-  const bool aligned = ((size_t)s->dp.Nx * sizeof(float)) % 128 == 0;
+  const bool aligned = ((size_t)s->dp.Nx * sizeof(T)) % 128 == 0;
   int nseg = 0;
   if (s->spread_order == 2 || (s->spread_order == 0 && !aligned)) {
     nseg = nwg / gx;
@@ -561,12 +630,11 @@ static void spread_mfma_impl(const fcmdp_solver* s, void* grid, hipStream_t st) 
     nwg = gx * nseg;
   }
   if (nwg > nblk) nwg = nblk;
-  hipLaunchKernelGGL((k_spread_mfma<NCH, BY, DT, FZ>), dim3(nwg), dim3(256), 0, st, s->dp,
-                     s->band, s->cell_start, s->pinfo, (const float*)s->pw,
-                     (const float*)s->pf, (const float*)s->psi,
-                     DT ? (const float*)s->pdw : nullptr,
-                     DT ? (const float*)s->dpsi : nullptr, FZ ? s->psi64 : nullptr,
-                     (float*)grid, FZ ? s->fzlo : nullptr, nseg);
+  hipLaunchKernelGGL((k_spread_mfma<T, NCH, BY, DT, FZ>), dim3(nwg), dim3(256), 0, st, s->dp,
+                     s->band, s->cell_start, s->pinfo, (const T*)s->pw,
+                     (const T*)s->pf, (const T*)s->psi, DT ? (const T*)s->pdw : nullptr,
+                     DT ? (const T*)s->dpsi : nullptr, FZ ? s->psi64 : nullptr,
+                     (T*)grid, FZ ? s->fzlo : nullptr, nseg);
 }
 
 hipError_t launch_spread_mfma(const fcmdp_solver* s, int n, void* grid, hipStream_t st) {
@@ -576,30 +644,40 @@ hipError_t launch_spread_mfma(const fcmdp_solver* s, int n, void* grid, hipStrea
   const bool dt = s->dp.dt_torque != 0, fz = !dt && s->dp.lowk_ns >= 0;
   int by = s->spread_block_rows;
   if (by == 0) {
-    const double fill = 0.78 * (dt ? SRec<true, false>::kCap : SRec<false, false>::kCap);
+    const double fill = 0.78 * (dt ? SRec<float, true, false>::kCap
+                                   : SRec<float, false, false>::kCap);
     by = (double)n * (22.0 * 38.0) <= fill * (double)s->dp.Nx * s->dp.Ny ? 16 : 8;
   }
   if (s->dp.Ny < 16 + 6) by = 8;
   if (dt) {
-    by == 16 ? spread_mfma_impl<3, 16, true>(s, grid, st)
-             : spread_mfma_impl<3, 8, true>(s, grid, st);
+    by == 16 ? spread_mfma_impl<float, 3, 16, true>(s, grid, st)
+             : spread_mfma_impl<float, 3, 8, true>(s, grid, st);
     return hipGetLastError();
   }
   const bool dip = s->dp.nch_in == 6;
+  if (!s->mixed) {
+    if (by == 16)
+      dip ? spread_mfma_impl<double, 6, 16>(s, grid, st)
+          : spread_mfma_impl<double, 3, 16>(s, grid, st);
+    else
+      dip ? spread_mfma_impl<double, 6, 8>(s, grid, st)
+          : spread_mfma_impl<double, 3, 8>(s, grid, st);
+    return hipGetLastError();
+  }
   if (fz) {
     // the slit channel's vertical force in FP64 (sc1m: 2.24 ms with the gather)
     if (by == 16)
-      dip ? spread_mfma_impl<6, 16, false, true>(s, grid, st)
-          : spread_mfma_impl<3, 16, false, true>(s, grid, st);
+      dip ? spread_mfma_impl<float, 6, 16, false, true>(s, grid, st)
+          : spread_mfma_impl<float, 3, 16, false, true>(s, grid, st);
     else
-      dip ? spread_mfma_impl<6, 8, false, true>(s, grid, st)
-          : spread_mfma_impl<3, 8, false, true>(s, grid, st);
+      dip ? spread_mfma_impl<float, 6, 8, false, true>(s, grid, st)
+          : spread_mfma_impl<float, 3, 8, false, true>(s, grid, st);
     return hipGetLastError();
   }
   if (by == 16)
-    dip ? spread_mfma_impl<6, 16>(s, grid, st) : spread_mfma_impl<3, 16>(s, grid, st);
+    dip ? spread_mfma_impl<float, 6, 16>(s, grid, st) : spread_mfma_impl<float, 3, 16>(s, grid, st);
   else
-    dip ? spread_mfma_impl<6, 8>(s, grid, st) : spread_mfma_impl<3, 8>(s, grid, st);
+    dip ? spread_mfma_impl<float, 6, 8>(s, grid, st) : spread_mfma_impl<float, 3, 8>(s, grid, st);
   return hipGetLastError();
 }
 
