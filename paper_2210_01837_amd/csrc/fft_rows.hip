@@ -104,6 +104,15 @@ __device__ __forceinline__ void row_plan(cplx_t<T>* lds, int S, int rows, const 
   }
 }
 
+// Row batch of workgroup b of n in an x-pass whose transposed runs are half a
+// 128-byte line: workgroups b and b + 8, which run on the same XCD one after
+// the other, take neighbouring batches, so that both halves of a line meet in
+// that XCD's L2.
+__device__ __forceinline__ int paired_batch(int b, int n) {
+  const int q = b & ~15, r = b & 15;
+  return q + 16 <= n ? q + 2 * (r & 7) + (r >> 3) : b;
+}
+
 struct RowArgs {
   int Nx, Ny, Nz, Nkx, rows;
   unsigned m_rows, m_len, m_half;   // quick divisors: rows (or row pairs), M, M / 2 + 1
@@ -122,7 +131,8 @@ k_rows_x_r2c(RowArgs ra, RowPlan pl, const int* __restrict__ band, const T* __re
   const int p = blockIdx.y, c = p % ra.Nz;
   if (c < band[0] || c > band[1]) return;
   const int M = ra.Nx / 2, S = (M + 1) | 1, rows = ra.rows, nt = blockDim.x;
-  const int y0 = blockIdx.x * rows, nr = min(rows, ra.Ny - y0);
+  const int yb = rows * (int)sizeof(C) == 64 ? paired_batch(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int y0 = yb * rows, nr = min(rows, ra.Ny - y0);
   const C* src = reinterpret_cast<const C*>(grid + ((size_t)p * ra.Ny + y0) * ra.Nx);
 #pragma unroll 4
   for (int e = threadIdx.x; e < nr * M; e += nt) {
@@ -179,7 +189,8 @@ k_rows_x_c2r(RowArgs ra, RowPlan pl, const int* __restrict__ band,
   const int p = blockIdx.y, c = p % ra.Nz;
   if (c < band[0] || c > band[1]) return;
   const int M = ra.Nx / 2, S = (M + 1) | 1, rows = ra.rows, nt = blockDim.x;
-  const int y0 = blockIdx.x * rows, nr = min(rows, ra.Ny - y0);
+  const int yb = rows * (int)sizeof(C) == 64 ? paired_batch(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int y0 = yb * rows, nr = min(rows, ra.Ny - y0);
   const C* src = spec + (size_t)p * ra.Nkx * ra.Ny + y0;
   if (sizeof(T) == 4 && rows % 2 == 0) {
     const int h = rows / 2;
@@ -336,8 +347,14 @@ static hipError_t rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* 
   const RowPlan& pl = s->rplan_x;
   const int M = dp.Nx / 2;
   const size_t row = ((size_t)(M + 1) | 1) * sizeof(C);
-  // 128-byte runs of the transposed side, fewer rows if LDS or threads run out
-  int rows = s->rows_x > 0 ? s->rows_x : (fp32 ? 16 : 8), nt = 0;
+  // Runs of a full 128-byte line on the transposed side, but half of one, in
+  // paired batches, where a CU's LDS holds three full batches or fewer: more
+  // workgroups to hide the barriers of each other.  Forward / inverse in us,
+  // full against half: 1176 points FP32 578/495 -> 565/476, 756 FP32 246/191 ->
+  // 219/173, 768 FP64 758/742 -> 738/677; with seven batches already there
+  // (360 FP32) 109/81 -> 112/82.  Fewer rows also if LDS or threads run out.
+  const int line = fp32 ? 16 : 8;
+  int rows = s->rows_x > 0 ? s->rows_x : 4 * line * row > kLdsBudget ? line / 2 : line, nt = 0;
   for (;; rows = rows == 12 ? 8 : rows / 2) {
     nt = rows * row <= kLdsBudget ? row_threads(pl, rows, rows * row, fp32) : 0;
     if (nt || rows == 1) break;
