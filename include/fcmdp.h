@@ -203,7 +203,7 @@ int fcmdp_lanczos_sqrt_noalloc(fcmdp_solver* s, int64_t n, const void* pos,
  * spectrum (4 (Nx/2+1) Ny complex words) is allocated on first use
  * (stream-ordered) and kept with the solver.  Like every call on one
  * solver, it must be ordered with the solver's other calls.  Returns
- * EINVAL for s == NULL or Nz > 32 (the eight-lane column kernels), EHIP.
+ * EINVAL for s == NULL or Nz > 32, EHIP.
  */
 int fcmdp_set_wall_velocity(fcmdp_solver* s, const void* wall, void* hip_stream);
 
@@ -230,8 +230,8 @@ int fcmdp_stage_times(fcmdp_solver* s, double ms[8], int64_t* napplies);
  * the sizes; the alternatives below compute the same quantities with a
  * different parallel decomposition and exist for cross-checks and tuning.
  * value: 0/1 for the switches; for the FFT row counts a power of two, or 12
- * for the x pass (rows per workgroup of the wave-per-row x and y passes,
- * 0 = default), rejected with FCMDP_EINVAL if the rows do not fit in LDS;
+ * for the x pass (rows per workgroup of the x and y passes, 0 = default: by
+ * the row's length), rejected with FCMDP_EINVAL if the rows do not fit in LDS;
  * for the spread's workgroups 1..65535, block rows 8 or 16 and block order
  * 1 or 2 (0 = default), else FCMDP_EINVAL.
  * Not thread safe with respect to applies on the same solver.
@@ -252,17 +252,17 @@ enum {
   FCMDP_VARIANT_NO_LOWK = 9,         /* MIXED slit channel: take the vertical
                                         force of the kH < 1 columns from the
                                         FP32 path too (no FP64 route) */
-  FCMDP_VARIANT_WAVE_SPREAD = 10,    /* MIXED: per-patch gather spread on the
-                                        vector units instead of the matrix-core
-                                        spread of the FP32 grid */
-  FCMDP_VARIANT_SPREAD_WORKGROUPS = 11, /* MIXED: workgroups of the
-                                        matrix-core spread, which share its
-                                        blocks evenly (1..65535; 0 = default,
-                                        three per CU: as many as fit at once) */
-  FCMDP_VARIANT_SPREAD_BLOCK_ROWS = 12, /* MIXED: grid rows per block of the
+  FCMDP_VARIANT_WAVE_SPREAD = 10,    /* per-patch gather spread on the vector
+                                        units instead of the matrix-core
+                                        spread */
+  FCMDP_VARIANT_SPREAD_WORKGROUPS = 11, /* workgroups of the matrix-core
+                                        spread, which share its blocks evenly
+                                        (1..65535; 0 = default, two or three
+                                        per CU: as many as fit at once) */
+  FCMDP_VARIANT_SPREAD_BLOCK_ROWS = 12, /* grid rows per block of the
                                         matrix-core spread (8 or 16; 0 =
                                         default, chosen by particle density) */
-  FCMDP_VARIANT_SPREAD_ORDER = 13,   /* MIXED: block order of the matrix-core
+  FCMDP_VARIANT_SPREAD_ORDER = 13,   /* block order of the matrix-core
                                         spread: 1 strip-major, shared evenly;
                                         2 neighbouring strips side by side;
                                         0 = default: 1 if grid rows are whole

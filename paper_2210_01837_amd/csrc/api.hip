@@ -134,8 +134,8 @@ int validate(const fcmdp_params* p) {
   if (p->w != 4 && p->w != 6) return FCMDP_EINVAL;
   if (p->max_particles < 0 || p->max_particles > (int64_t)1 << 30)
     return FCMDP_EINVAL;
-  // partial slip, solved by the eight-lane column kernels; a bottom wall
-  // has a slip length at z = 0 only
+  // partial slip: Nz <= 32, the sizes that it is tested at; a bottom wall has
+  // a slip length at z = 0 only
   if (!(p->slip0 >= 0) || !(p->slipH >= 0) || !std::isfinite(p->slip0) ||
       !std::isfinite(p->slipH))
     return FCMDP_EINVAL;
@@ -620,7 +620,7 @@ int fcmdp_set_wall_velocity(fcmdp_solver* s, const void* wall,
     s->dp.wallspec = nullptr;
     return FCMDP_OK;
   }
-  // the wall data enter the eight-lane column kernels only
+  // like the slip, at the sizes that it is tested at
   if (s->dp.Nz > 32) return FCMDP_EINVAL;
   hipStream_t st = (hipStream_t)hip_stream;
   const size_t csz = s->mixed ? 8 : 16;

@@ -26,9 +26,7 @@
 // each lane with one parity of one real column,
 //   lane = 16 (2 parity + imaginary) + column,  NA coefficients 2 i + parity,
 // and the tridiagonal half-systems of the BVPs become plain sequential sweeps
-// in registers, the same in every lane (no scans and no lane moves; eight
-// lanes per column with segmented scans took 3.4 times the instructions per
-// column).  What couples the parities (B of a series, sums at the walls) is
+// in registers, the same in every lane (no scans and no lane moves).  What couples the parities (B of a series, sums at the walls) is
 // exchanged with v_permlane32_swap.  The inverse transform reads the same
 // registers as B operands after the opposite swap, and a lane ends with the
 // complex values of its column at four nodes per tile: 128-byte runs per
@@ -36,6 +34,13 @@
 //
 // z-derivatives on the right-hand sides are taken through B^2 D = B, i.e.
 // (f_{m-1} - f_{m+1}) / (2 m): no recurrence over the coefficients.
+//
+// Bound by the FP64 instructions of the sweeps, two wavefronts per SIMD (256
+// registers, none spilled).  Against eight lanes per column with segmented
+// scans (and, for FP64 data or Nz > 32, one thread per column in scratch), one
+// launch: 2176^2, 20 planes, mixed 3.37 -> 1.62 ms; two walls 4.39 -> 1.9;
+// 2700^2 forces only 3.34 -> 1.6; 768^2 0.43 -> 0.22; in FP64 1.41 -> 0.46;
+// 192^2, Nz = 48, FP64 6.2 -> 0.12.
 #include <algorithm>
 #include <type_traits>
 
@@ -989,7 +994,8 @@ hipError_t launch_columns_mfma(const fcmdp_solver* s, const void* spec_in,
   cp.dctf = s->dct_f;
   cp.iH = 1.0 / s->dp.H;
   cp.s2H = 2.0 / s->dp.H;
-  // the smallest half-length that holds ceil(Nz / 2) coefficients per parity
+  // the smallest half-length that holds ceil(Nz / 2) coefficients per parity:
+  // 10 for the 19 nodes of a 2700^2 layer, FP32 data; 16 would sweep 60% more
   const int Nz = s->dp.Nz;
   if (s->mixed && Nz <= 32 && !s->force_vector_dct) {
     if (Nz <= 20) launch_geometry<float, float, 2, 10>(s, cp, spec_in, spec_out, st);

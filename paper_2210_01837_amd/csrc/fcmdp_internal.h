@@ -169,14 +169,14 @@ struct fcmdp_solver {
   bool force_halo_interp = false;
   // use the untiled gather spread (tests)
   bool force_simple_spread = false;
-  // use the per-patch gather spread instead of the matrix-core spread of the
-  // FP32 grid (tests), the workgroups of the latter (0: three per CU, the
-  // number that fit at once) and its rows per block (0: by density)
+  // use the per-patch gather spread instead of the matrix-core spread (tests),
+  // the workgroups of the latter (0: two or three per CU, the number that fit
+  // at once) and its rows per block (0: by density)
   bool force_wave_spread = false;
   int spread_workgroups = 0;
   int spread_block_rows = 0;
   int spread_order = 0;         // 0: by row alignment, 1: strip-major, 2: strips side by side
-  // use the per-lane FP64 Chebyshev transforms in the mixed path (tests)
+  // use FP64 Chebyshev transforms in the mixed path (tests)
   bool force_vector_dct = false;
   // use the workgroup-per-row-batch transforms (tests)
   bool force_generic_fft = false;

@@ -98,7 +98,9 @@ k_spread(DevParams dp, const int* __restrict__ band,
   }
 }
 
-// Wave-uniform spread: a wavefront owns an 8 x 8 patch of grid columns and
+// Wave-uniform spread, where spread_mfma.hip does not go: derivative torques in
+// FP64 or with the vertical force in FP64, and grids smaller than a block's
+// region.  A wavefront owns an 8 x 8 patch of grid columns and
 // walks, in cell-sorted order, every particle of the 14 x 14 cells whose
 // kernels can reach the patch.  The particle is the same on all lanes; each
 // lane adds its contribution to its own column when that column lies in the

@@ -37,16 +37,20 @@ CSRC = os.path.join(PKG, "csrc")
 
 # translation unit (plus the headers it includes) of each profiled kernel
 KERNEL_SOURCES = {
-    "k_columns_mfma": ["columns_seg.hip", "colmath.h", "fcmdp_internal.h"],
+    "k_columns_mfma": ["columns_mfma.hip", "colmath.h", "fcmdp_internal.h"],
     "k_spread_wave": ["spread_interp.hip", "es.h", "fcmdp_internal.h"],
     "k_spread_mfma": ["spread_mfma.hip", "fcmdp_internal.h"],
     "k_interp_tiled": ["spread_interp.hip", "es.h", "fcmdp_internal.h"],
     "k_interp_part": ["interp_part.hip", "fcmdp_internal.h"],
     "k_interp_sum": ["interp_part.hip", "fcmdp_internal.h"],
-    "k_fftw_x_r2c": ["fft.hip", "fcmdp_internal.h"],
-    "k_fftw_y": ["fft.hip", "fcmdp_internal.h"],
-    "k_fftw_y_pipe": ["fft.hip", "fcmdp_internal.h"],
-    "k_fftw_x_c2r": ["fft.hip", "fcmdp_internal.h"],
+    "k_interp_wave": ["interp_wave.hip", "fcmdp_internal.h"],
+    "k_fftw_x_r2c": ["fft.hip", "dft.h", "fcmdp_internal.h"],
+    "k_fftw_y": ["fft.hip", "dft.h", "fcmdp_internal.h"],
+    "k_fftw_y_pipe": ["fft.hip", "dft.h", "fcmdp_internal.h"],
+    "k_fftw_x_c2r": ["fft.hip", "dft.h", "fcmdp_internal.h"],
+    "k_rows_x_r2c": ["fft_rows.hip", "dft.h", "fcmdp_internal.h"],
+    "k_rows_y": ["fft_rows.hip", "dft.h", "fcmdp_internal.h"],
+    "k_rows_x_c2r": ["fft_rows.hip", "dft.h", "fcmdp_internal.h"],
     "k_records": ["prep.hip", "es.h", "fcmdp_internal.h"],
 }
 
