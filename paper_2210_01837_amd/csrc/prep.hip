@@ -396,7 +396,9 @@ k_small_sort(DevParams dp, int n, const Tin* __restrict__ pos, const double* __r
 // the position of the first and of the past-the-end cell by a 128-ary search
 // over all keys (three rounds for two million; a binary search is a chain of
 // twenty dependent loads), then the threads search the keys between the two,
-// in LDS where they fit.
+// in LDS where they fit.  These workgroups come first in the launch of
+// k_records, which reads only the sorted keys too: as a kernel of their own they
+// took 4 us of a small call's 125 and 19 us at 1M particles.
 constexpr int kCellBlock = 1024, kCellKeys = 2048;
 template <typename Keys>
 __device__ __forceinline__ int lower_bound(const Keys& keys, int lo, int hi, uint32_t c) {
@@ -406,12 +408,12 @@ __device__ __forceinline__ int lower_bound(const Keys& keys, int lo, int hi, uin
   }
   return lo;
 }
-__global__ void __launch_bounds__(256)
-k_cell_start(int n, int ncells, const uint32_t* __restrict__ keys,
-             int* __restrict__ cell_start) {
+__device__ __forceinline__ void cell_starts(int block, int n, int ncells,
+                                            const uint32_t* __restrict__ keys,
+                                            int* __restrict__ cell_start) {
   __shared__ int cnt[2][2];
   __shared__ uint32_t sk[kCellKeys];
-  const int c0 = blockIdx.x * kCellBlock;
+  const int c0 = block * kCellBlock;
   const int side = threadIdx.x >> 7, t = threadIdx.x & 127;
   const uint32_t c = (uint32_t)(c0 + side * kCellBlock);
   int lo = 0, hi = n;                              // the answer is in [lo, hi]
@@ -445,8 +447,7 @@ k_cell_start(int n, int ncells, const uint32_t* __restrict__ keys,
   }
 }
 
-// Keys, band and domain errors of all particles, then the sort (keyA, valA) and
-// the cell starts.
+// Keys, band and domain errors of all particles, then the sort (keyA, valA).
 template <typename Tin>
 static void sort_impl(const fcmdp_solver* s, int n, const Tin* pos, hipStream_t st) {
   if (n > 0 && n <= kSmallSort) {
@@ -486,11 +487,9 @@ static void sort_impl(const fcmdp_solver* s, int n, const Tin* pos, hipStream_t 
       std::swap(vin, vout);
     }
   }
-  hipLaunchKernelGGL(k_cell_start, dim3(s->dp.ncells / kCellBlock + 1), dim3(256), 0, st, n,
-                     s->dp.ncells, s->keyA, s->cell_start);
 }
 
-// Keys to cell starts, against one histogram, scan and scatter kernel per pass
+// Keys and sort, with the cell starts, against one histogram, scan and scatter kernel per pass
 // with a serial scan of the workgroup totals and a final copy: 61 -> 23 us at
 // 1031 particles, 110 -> 63 at 17k, 125 -> 74 at 131k, 245 -> 141 at 1M.  Bound
 // by launches up to some 10^5 particles, then by the scattered writes.
@@ -525,12 +524,17 @@ k_records(DevParams dp, int n, const uint32_t* __restrict__ skeys,
           const Tin* __restrict__ F, const Tin* __restrict__ Tq,
           const double* __restrict__ zc, int4* __restrict__ pinfo,
           T* __restrict__ pw, T* __restrict__ pf, T* __restrict__ psi,
-          double* __restrict__ psi64, T* __restrict__ pdw, T* __restrict__ dpsi) {
+          double* __restrict__ psi64, T* __restrict__ pdw, T* __restrict__ dpsi,
+          int cell_blocks, int* __restrict__ cell_start) {
+  if ((int)blockIdx.x < cell_blocks) {               // whole workgroup
+    cell_starts(blockIdx.x, n, dp.ncells, skeys, cell_start);
+    return;
+  }
   // four lanes per particle (its quad): lane q writes x/y weight part q,
   // the z weights of the node groups q, q + 4, ... (four nodes each) and
   // its share of the other records, so that the kernel evaluations of one
   // particle run in four independent chains
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+  const int gid = (blockIdx.x - cell_blocks) * blockDim.x + threadIdx.x;
   const int i = gid >> 2, q = gid & 3;
   if (i >= n) return;
   const int Nz = dp.Nz;
@@ -679,13 +683,15 @@ k_records(DevParams dp, int n, const uint32_t* __restrict__ skeys,
 template <typename Tin, typename T>
 static void records_impl(const fcmdp_solver* s, int n, const void* pos,
                          const void* F, const void* Tq, hipStream_t st) {
-  hipLaunchKernelGGL((k_records<Tin, T>), dim3((4 * (size_t)n + 255) / 256), dim3(256), 0,
-                     st, s->dp, n, s->keyA, s->valA, (const Tin*)pos,
+  const int cell_blocks = s->dp.ncells / kCellBlock + 1;
+  hipLaunchKernelGGL((k_records<Tin, T>), dim3(cell_blocks + (4 * (size_t)n + 255) / 256),
+                     dim3(256), 0, st, s->dp, n, s->keyA, s->valA, (const Tin*)pos,
                      (const Tin*)F, (const Tin*)Tq, s->zc, s->pinfo,
                      (T*)s->pw, (T*)s->pf, (T*)s->psi,
                      s->dp.lowk_ns >= 0 ? s->psi64 : nullptr,
                      (s->dp.dt_torque || s->dp.dt_omega) ? (T*)s->pdw : nullptr,
-                     (s->dp.dt_torque || s->dp.dt_omega) ? (T*)s->dpsi : nullptr);
+                     (s->dp.dt_torque || s->dp.dt_omega) ? (T*)s->dpsi : nullptr,
+                     cell_blocks, s->cell_start);
 }
 
 // The forces of the records alone, for another apply on the same positions.
