@@ -250,12 +250,13 @@ int fft_codelet(int n, bool fp32);
 // LDS elements per row of the transforms of length n (x: Nx/2, with room for
 // the Nyquist element; y: Ny) for fixed plan `codelet` (-1: run-time plan)
 int fft_lds_row(int codelet, int n, bool x);
-// fft_rows.hip: row transforms by run-time plans
+// fft_rows.hip: row transforms of nch channels by run-time plans
 bool make_row_plan(int n, bool fp32, RowPlan* pl);
 bool row_plan_fits(const RowPlan& pl, bool fp32);
-hipError_t launch_rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+hipError_t launch_rows_x(bool fwd, const fcmdp_solver* s, int nch, const void* in,
+                         void* out, hipStream_t st);
+hipError_t launch_rows_y(const fcmdp_solver* s, int nch, void* spec, int sign,
                          hipStream_t st);
-hipError_t launch_rows_y(const fcmdp_solver* s, void* spec, int sign, hipStream_t st);
 // columns.hip (one thread per column, a cross-check); columns_mfma.hip
 hipError_t launch_columns(const fcmdp_solver* s, const void* spec_in,
                           void* spec_out, hipStream_t st);

@@ -656,13 +656,13 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
 }
 
 template <typename T, int ROWS, int TPR, typename Run>
-static void launch_wave_x(bool fwd, const fcmdp_solver* s, const void* in,
+static void launch_wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* in,
                           void* out, const DftOff& doff, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   const int M = dp.Nx / 2;
   const size_t lds = (size_t)ROWS * x_stride<Run>(M) * sizeof(C);
-  dim3 g((dp.Ny + ROWS - 1) / ROWS, (fwd ? dp.nch_in : dp.nch_out) * dp.Nz);
+  dim3 g((dp.Ny + ROWS - 1) / ROWS, nch * dp.Nz);
   const T* cs = (const T*)s->dftc_t;
   if (fwd)
     hipLaunchKernelGGL((k_fftw_x_r2c<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR),
@@ -683,7 +683,7 @@ static int rows_fitting(size_t row_bytes, int maxrows) {
   return r;
 }
 template <typename T, int TPR, typename Run>
-static void wave_x_rows(bool fwd, const fcmdp_solver* s, const void* in,
+static void wave_x_rows(bool fwd, const fcmdp_solver* s, int nch, const void* in,
                         void* out, const DftOff& doff, hipStream_t st) {
   const size_t row = (size_t)x_stride<Run>(s->dp.Nx / 2) * sizeof(cplx_t<T>);
   int r = s->rows_x;
@@ -692,43 +692,43 @@ static void wave_x_rows(bool fwd, const fcmdp_solver* s, const void* in,
     if (r == 8 && 12 * row <= kLdsBudget) r = 12;
   }
   switch (r) {
-    case 16: launch_wave_x<T, 16, 64, Run>(fwd, s, in, out, doff, st); break;
-    case 12: launch_wave_x<T, 12, 64, Run>(fwd, s, in, out, doff, st); break;
-    case 8: launch_wave_x<T, 8, TPR, Run>(fwd, s, in, out, doff, st); break;
-    case 4: launch_wave_x<T, 4, TPR, Run>(fwd, s, in, out, doff, st); break;
-    case 2: launch_wave_x<T, 2, TPR, Run>(fwd, s, in, out, doff, st); break;
-    default: launch_wave_x<T, 1, TPR, Run>(fwd, s, in, out, doff, st); break;
+    case 16: launch_wave_x<T, 16, 64, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 12: launch_wave_x<T, 12, 64, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 8: launch_wave_x<T, 8, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 4: launch_wave_x<T, 4, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 2: launch_wave_x<T, 2, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
+    default: launch_wave_x<T, 1, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
   }
 }
 
 template <typename T, int ROWS, int TPR, typename Run>
-static void launch_wave_y(const fcmdp_solver* s, void* spec, const DftOff& doff,
+static void launch_wave_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                           T sign, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   const size_t lds = (size_t)ROWS * Run::span(dp.Ny) * sizeof(C);
-  dim3 g((dp.Nkx + ROWS - 1) / ROWS, (sign < 0 ? dp.nch_in : dp.nch_out) * dp.Nz);
+  dim3 g((dp.Nkx + ROWS - 1) / ROWS, nch * dp.Nz);
   hipLaunchKernelGGL((k_fftw_y<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR), lds, st,
                      dp, s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
                      (const T*)s->dftc_t, doff, sign);
 }
 
 template <typename T, int TPR, typename Run>
-static void wave_y_rows(const fcmdp_solver* s, void* spec, const DftOff& doff,
+static void wave_y_rows(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                         T sign, hipStream_t st) {
   // rows are independent; one per workgroup packs LDS best
   switch (s->rows_y) {
-    case 8: launch_wave_y<T, 8, TPR, Run>(s, spec, doff, sign, st); break;
-    case 4: launch_wave_y<T, 4, TPR, Run>(s, spec, doff, sign, st); break;
-    case 2: launch_wave_y<T, 2, TPR, Run>(s, spec, doff, sign, st); break;
-    default: launch_wave_y<T, 1, TPR, Run>(s, spec, doff, sign, st); break;
+    case 8: launch_wave_y<T, 8, TPR, Run>(s, nch, spec, doff, sign, st); break;
+    case 4: launch_wave_y<T, 4, TPR, Run>(s, nch, spec, doff, sign, st); break;
+    case 2: launch_wave_y<T, 2, TPR, Run>(s, nch, spec, doff, sign, st); break;
+    default: launch_wave_y<T, 1, TPR, Run>(s, nch, spec, doff, sign, st); break;
   }
 }
 
 // Persistent y-pass: as many one-wavefront workgroups as stay resident (LDS
 // and registers allow eight per compute unit).
 template <typename T, typename Run>
-static void wave_y_pipe(const fcmdp_solver* s, void* spec, const DftOff& doff,
+static void wave_y_pipe(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                         T sign, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
@@ -738,7 +738,7 @@ static void wave_y_pipe(const fcmdp_solver* s, void* spec, const DftOff& doff,
   hipLaunchKernelGGL((k_fftw_y_pipe<T, Run>), dim3(g), dim3(64), lds, st, dp,
                      s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
                      (const T*)s->dftc_t, doff, sign,
-                     sign < 0 ? dp.nch_in : dp.nch_out);
+                     nch);
 }
 
 // Codelets compiled for the transform lengths of the large workloads (single
@@ -756,40 +756,40 @@ using Codelet5 = FixedRows<3 * 16 + 15, 3 * 16 + 15, 3 * 16 + 15, 5 * 16 + 9,
                            5 * 16 + 9, 4 * 16 + 11>;
 
 template <typename T>
-static void wave_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+static void wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                    const DftOff& doff, hipStream_t st) {
   switch (s->codelet_x) {
-    case 0: wave_x_rows<T, 64, Codelet0>(fwd, s, in, out, doff, st); return;
-    case 1: wave_x_rows<T, 64, Codelet1>(fwd, s, in, out, doff, st); return;
-    case 2: wave_x_rows<T, 64, Codelet2>(fwd, s, in, out, doff, st); return;
-    case 3: wave_x_rows<T, 64, Codelet3>(fwd, s, in, out, doff, st); return;
-    case 4: wave_x_rows<T, 64, Codelet4>(fwd, s, in, out, doff, st); return;
-    case 5: wave_x_rows<T, 64, Codelet5>(fwd, s, in, out, doff, st); return;
+    case 0: wave_x_rows<T, 64, Codelet0>(fwd, s, nch, in, out, doff, st); return;
+    case 1: wave_x_rows<T, 64, Codelet1>(fwd, s, nch, in, out, doff, st); return;
+    case 2: wave_x_rows<T, 64, Codelet2>(fwd, s, nch, in, out, doff, st); return;
+    case 3: wave_x_rows<T, 64, Codelet3>(fwd, s, nch, in, out, doff, st); return;
+    case 4: wave_x_rows<T, 64, Codelet4>(fwd, s, nch, in, out, doff, st); return;
+    case 5: wave_x_rows<T, 64, Codelet5>(fwd, s, nch, in, out, doff, st); return;
     default: break;
   }
 }
 
 template <typename T>
-static void wave_y(const fcmdp_solver* s, void* spec, const DftOff& doff,
+static void wave_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                          T sign, hipStream_t st) {
   if (!s->force_no_pipeline) {
     switch (s->codelet_y) {
-      case 0: wave_y_pipe<T, Codelet0>(s, spec, doff, sign, st); return;
-      case 1: wave_y_pipe<T, Codelet1>(s, spec, doff, sign, st); return;
-      case 2: wave_y_pipe<T, Codelet2>(s, spec, doff, sign, st); return;
-      case 3: wave_y_pipe<T, Codelet3>(s, spec, doff, sign, st); return;
-      case 4: wave_y_pipe<T, Codelet4>(s, spec, doff, sign, st); return;
-      case 5: wave_y_pipe<T, Codelet5>(s, spec, doff, sign, st); return;
+      case 0: wave_y_pipe<T, Codelet0>(s, nch, spec, doff, sign, st); return;
+      case 1: wave_y_pipe<T, Codelet1>(s, nch, spec, doff, sign, st); return;
+      case 2: wave_y_pipe<T, Codelet2>(s, nch, spec, doff, sign, st); return;
+      case 3: wave_y_pipe<T, Codelet3>(s, nch, spec, doff, sign, st); return;
+      case 4: wave_y_pipe<T, Codelet4>(s, nch, spec, doff, sign, st); return;
+      case 5: wave_y_pipe<T, Codelet5>(s, nch, spec, doff, sign, st); return;
       default: break;
     }
   }
   switch (s->codelet_y) {
-    case 0: wave_y_rows<T, 64, Codelet0>(s, spec, doff, sign, st); return;
-    case 1: wave_y_rows<T, 64, Codelet1>(s, spec, doff, sign, st); return;
-    case 2: wave_y_rows<T, 64, Codelet2>(s, spec, doff, sign, st); return;
-    case 3: wave_y_rows<T, 64, Codelet3>(s, spec, doff, sign, st); return;
-    case 4: wave_y_rows<T, 64, Codelet4>(s, spec, doff, sign, st); return;
-    case 5: wave_y_rows<T, 64, Codelet5>(s, spec, doff, sign, st); return;
+    case 0: wave_y_rows<T, 64, Codelet0>(s, nch, spec, doff, sign, st); return;
+    case 1: wave_y_rows<T, 64, Codelet1>(s, nch, spec, doff, sign, st); return;
+    case 2: wave_y_rows<T, 64, Codelet2>(s, nch, spec, doff, sign, st); return;
+    case 3: wave_y_rows<T, 64, Codelet3>(s, nch, spec, doff, sign, st); return;
+    case 4: wave_y_rows<T, 64, Codelet4>(s, nch, spec, doff, sign, st); return;
+    case 5: wave_y_rows<T, 64, Codelet5>(s, nch, spec, doff, sign, st); return;
     default: break;
   }
 }
@@ -831,12 +831,12 @@ static DftOff dft_offsets(const fcmdp_solver* s) {
 // Passes with workgroup-owned rows, two buffers and radices up to 8 (a
 // cross-check: variant FCMDP_VARIANT_GENERIC_FFT).
 template <typename T>
-static void generic_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+static void generic_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                       const DftOff& doff, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   const int M = dp.Nx / 2;
-  const int planes = (fwd ? dp.nch_in : dp.nch_out) * dp.Nz;
+  const int planes = nch * dp.Nz;
   int rows = rows_for(M, sizeof(C), fwd ? 0 : 1, 16);
   if (rows > dp.Ny) rows = dp.Ny;
   const dim3 g((dp.Ny + rows - 1) / rows, planes);
@@ -851,13 +851,13 @@ static void generic_x(bool fwd, const fcmdp_solver* s, const void* in, void* out
                        doff, rows);
 }
 template <typename T>
-static void generic_y(const fcmdp_solver* s, void* spec, const DftOff& doff, T sign,
+static void generic_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff, T sign,
                       hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   int rows = rows_for(dp.Ny, sizeof(C), 0, 16);
   if (rows > dp.Nkx) rows = dp.Nkx;
-  const int planes = (sign < 0 ? dp.nch_in : dp.nch_out) * dp.Nz;
+  const int planes = nch * dp.Nz;
   hipLaunchKernelGGL(k_fft_y<T>, dim3((dp.Nkx + rows - 1) / rows, planes), dim3(256),
                      2 * (size_t)rows * dp.Ny * sizeof(C), st, dp, s->plan_y, s->band,
                      (C*)spec, (const C*)s->tw_y, s->dftc, doff, rows, sign);
@@ -865,42 +865,80 @@ static void generic_y(const fcmdp_solver* s, void* spec, const DftOff& doff, T s
 
 // One pass: the fixed plan of the length where there is one, else the run-time
 // plan of fft_rows.hip.
-static hipError_t x_pass(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+static hipError_t x_pass(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                          hipStream_t st) {
   const DftOff doff = dft_offsets(s);
   if (s->force_generic_fft) {
-    if (s->mixed) generic_x<float>(fwd, s, in, out, doff, st);
-    else generic_x<double>(fwd, s, in, out, doff, st);
+    if (s->mixed) generic_x<float>(fwd, s, nch, in, out, doff, st);
+    else generic_x<double>(fwd, s, nch, in, out, doff, st);
   } else if (s->codelet_x >= 0) {
-    wave_x<float>(fwd, s, in, out, doff, st);
+    wave_x<float>(fwd, s, nch, in, out, doff, st);
   } else {
-    return launch_rows_x(fwd, s, in, out, st);
+    return launch_rows_x(fwd, s, nch, in, out, st);
   }
   return hipGetLastError();
 }
-static hipError_t y_pass(const fcmdp_solver* s, void* spec, int sign, hipStream_t st) {
+static hipError_t y_pass(const fcmdp_solver* s, int nch, void* spec, int sign, hipStream_t st) {
   const DftOff doff = dft_offsets(s);
   if (s->force_generic_fft) {
-    if (s->mixed) generic_y<float>(s, spec, doff, (float)sign, st);
-    else generic_y<double>(s, spec, doff, (double)sign, st);
+    if (s->mixed) generic_y<float>(s, nch, spec, doff, (float)sign, st);
+    else generic_y<double>(s, nch, spec, doff, (double)sign, st);
   } else if (s->codelet_y >= 0) {
-    wave_y<float>(s, spec, doff, (float)sign, st);
+    wave_y<float>(s, nch, spec, doff, (float)sign, st);
   } else {
-    return launch_rows_y(s, spec, sign, st);
+    return launch_rows_y(s, nch, spec, sign, st);
   }
   return hipGetLastError();
+}
+
+// Channels per group of an x- and a y-pass that run one after the other on it.
+// A group whose planes stay in the 256 MB last-level cache between the two saves
+// the second its reads from HBM; each further pair of launches costs its
+// drained ends.  The band is known to the device only; usually it is half of
+// the Nz planes.  Forward / inverse in us, all channels against groups: 768^2
+// FP64 (151 MB a channel) 745/682 -> 672/654 by two; 1176^2 FP32 (177 MB)
+// 562/476 -> 525/490 by one; 768^2 FP32 (76 MB) 310/301 -> 293/294 by three; but
+// 756 x 442 (217 MB all channels) 223/174 -> 241/191 and 2176^2 (606 MB a
+// channel) 2217/2394 -> 2584/2659 by one.
+static int fft_group(const fcmdp_solver* s, int nch) {
+  const double mb = (s->mixed ? 8e-6 : 16e-6) * s->dp.Nz * s->dp.Nkx * s->dp.Ny;
+  const double fits = 320;
+  if (mb * nch <= fits || mb > fits) return nch;
+  const int most = (int)(fits / mb), groups = (nch + most - 1) / most;
+  return (nch + groups - 1) / groups;
 }
 
 hipError_t launch_fft_forward(const fcmdp_solver* s, const void* grid,
                               void* spec, hipStream_t st) {
-  const hipError_t e = x_pass(true, s, grid, spec, st);
-  return e != hipSuccess ? e : y_pass(s, spec, -1, st);
+  const DevParams& dp = s->dp;
+  const size_t t = s->mixed ? 4 : 8;
+  const size_t ch_grid = t * dp.Nz * dp.Ny * dp.Nx, ch_spec = 2 * t * dp.Nz * dp.Nkx * dp.Ny;
+  const int group = fft_group(s, dp.nch_in);
+  hipError_t e = hipSuccess;
+  for (int c = 0; c < dp.nch_in && e == hipSuccess; c += group) {
+    const int nch = std::min(group, dp.nch_in - c);
+    void* q = (char*)spec + c * ch_spec;
+    e = x_pass(true, s, nch, (const char*)grid + c * ch_grid, q, st);
+    if (e == hipSuccess) e = y_pass(s, nch, q, -1, st);
+  }
+  return e;
 }
 
 hipError_t launch_fft_inverse(const fcmdp_solver* s, void* spec, void* grid,
                               hipStream_t st) {
-  const hipError_t e = y_pass(s, spec, 1, st);
-  return e != hipSuccess ? e : x_pass(false, s, spec, grid, st);
+  const DevParams& dp = s->dp;
+  const size_t t = s->mixed ? 4 : 8;
+  const size_t ch_grid = t * dp.Nz * dp.Ny * dp.Nx, ch_spec = 2 * t * dp.Nz * dp.Nkx * dp.Ny;
+  // (in FP32 the inverse gains nothing from groups)
+  const int group = s->mixed ? dp.nch_out : fft_group(s, dp.nch_out);
+  hipError_t e = hipSuccess;
+  for (int c = 0; c < dp.nch_out && e == hipSuccess; c += group) {
+    const int nch = std::min(group, dp.nch_out - c);
+    void* q = (char*)spec + c * ch_spec;
+    e = y_pass(s, nch, q, 1, st);
+    if (e == hipSuccess) e = x_pass(false, s, nch, q, (char*)grid + c * ch_grid, st);
+  }
+  return e;
 }
 
 }  // namespace fcmdp

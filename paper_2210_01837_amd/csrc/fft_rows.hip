@@ -343,7 +343,7 @@ static RowArgs row_args(const fcmdp_solver* s, int rows, int pair) {
 }
 
 template <typename T>
-static hipError_t rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+static hipError_t rows_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                          hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
@@ -367,7 +367,7 @@ static hipError_t rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* 
   DftOff doff;
   for (int i = 0; i < 32; ++i) doff.off[i] = s->dft_off[i];
   const RowArgs ra = row_args(s, rows, fp32 && rows % 2 == 0);
-  const dim3 g((dp.Ny + rows - 1) / rows, (fwd ? dp.nch_in : dp.nch_out) * dp.Nz);
+  const dim3 g((dp.Ny + rows - 1) / rows, nch * dp.Nz);
   if (fwd)
     hipLaunchKernelGGL(k_rows_x_r2c<T>, g, dim3(nt), rows * row, st, ra, pl, s->band,
                        (const T*)in, (C*)out, (const C*)s->tws_x, (const C*)s->tw_r,
@@ -380,7 +380,7 @@ static hipError_t rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* 
 }
 
 template <typename T>
-static hipError_t rows_y(const fcmdp_solver* s, void* spec, int sign, hipStream_t st) {
+static hipError_t rows_y(const fcmdp_solver* s, int nch, void* spec, int sign, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   const bool fp32 = sizeof(T) == 4;
@@ -397,18 +397,19 @@ static hipError_t rows_y(const fcmdp_solver* s, void* spec, int sign, hipStream_
   DftOff doff;
   for (int i = 0; i < 32; ++i) doff.off[i] = s->dft_off[i];
   const RowArgs ra = row_args(s, rows, 0);
-  const dim3 g((dp.Nkx + rows - 1) / rows, (sign < 0 ? dp.nch_in : dp.nch_out) * dp.Nz);
+  const dim3 g((dp.Nkx + rows - 1) / rows, nch * dp.Nz);
   hipLaunchKernelGGL(k_rows_y<T>, g, dim3(nt), rows * row, st, ra, pl, s->band, (C*)spec,
                      (const C*)s->tws_y, (const T*)s->dftc_t, doff, T(sign));
   return hipGetLastError();
 }
 
-hipError_t launch_rows_x(bool fwd, const fcmdp_solver* s, const void* in, void* out,
+hipError_t launch_rows_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                          hipStream_t st) {
-  return s->mixed ? rows_x<float>(fwd, s, in, out, st) : rows_x<double>(fwd, s, in, out, st);
+  return s->mixed ? rows_x<float>(fwd, s, nch, in, out, st)
+                  : rows_x<double>(fwd, s, nch, in, out, st);
 }
-hipError_t launch_rows_y(const fcmdp_solver* s, void* spec, int sign, hipStream_t st) {
-  return s->mixed ? rows_y<float>(s, spec, sign, st) : rows_y<double>(s, spec, sign, st);
+hipError_t launch_rows_y(const fcmdp_solver* s, int nch, void* spec, int sign, hipStream_t st) {
+  return s->mixed ? rows_y<float>(s, nch, spec, sign, st) : rows_y<double>(s, nch, spec, sign, st);
 }
 
 // whether every stage of the pass fits a workgroup, one row at a time
