@@ -353,11 +353,7 @@ __device__ __forceinline__ void stage_fixed(cplx_t<T>* row, int t,
           x[q] = cmul(x[q], w);
         }
       }
-      if constexpr (R == 2) dft2<T, C>(x);
-      else if constexpr (R == 4) dft4<T, C>(x, sign);
-      else if constexpr (R == 8) dft8<T, C>(x, sign);
-      else if constexpr (R == 16) dft16<T, C>(x, sign);
-      else dft_prime<T, C, R>(x, cs, sign);
+      dft_any<T, C, R>(x, cs, sign);
       const int out = (j - k) * R + k;
       const int base = (int)((unsigned)out / BO) * PO + out;
 #pragma unroll
@@ -743,17 +739,18 @@ static void wave_y_pipe(const fcmdp_solver* s, int nch, void* spec, const DftOff
 
 // Codelets compiled for the transform lengths of the large workloads (single
 // precision, 64 threads per row); Codelet<i> has length kCodeletLength[i].
+// Few stages of large radices, the odd ones first: a stage is a round trip of the
+// row through LDS, and composite radices cost little arithmetic.  Forward /
+// inverse transforms, 2700 = 3 3 3 5 5 4 with 1350 = 3 3 3 5 5 2 against
+// 15 15 12 and 15 9 10: 2.02/2.19 -> 1.53/1.60 ms (13 planes, three channels);
+// 768 = 4 8 8 3 against 12 8 8: 293/294 -> 277/279 us (18 planes, six).
 static const int kCodeletLength[] = {1088, 2176, 384, 768, 1350, 2700};
 using Codelet0 = FixedRows<8 * 16 + 3, 8 * 16 + 3, 17 * 16 + 1>;
 using Codelet1 = FixedRows<16 * 16 + 3, 8 * 16 + 5, 17 * 16 + 2>;
 using Codelet2 = FixedRows<16 * 16 + 1, 8 * 16 + 1, 3 * 16 + 2>;
-using Codelet3 = FixedRows<4 * 16 + 3, 8 * 16 + 2, 8 * 16 + 2, 3 * 16 + 4>;
-// (odd radices first: 2.6 -> 1.9 ms per forward transform of the
-// forces-only layer against the power-of-two radix first)
-using Codelet4 = FixedRows<3 * 16 + 8, 3 * 16 + 8, 3 * 16 + 8, 5 * 16 + 5,
-                           5 * 16 + 5, 2 * 16 + 11>;
-using Codelet5 = FixedRows<3 * 16 + 15, 3 * 16 + 15, 3 * 16 + 15, 5 * 16 + 9,
-                           5 * 16 + 9, 4 * 16 + 11>;
+using Codelet3 = FixedRows<12 * 16 + 1, 8 * 16 + 2, 8 * 16 + 2>;
+using Codelet4 = FixedRows<15 * 16 + 2, 9 * 16 + 3, 10 * 16 + 3>;
+using Codelet5 = FixedRows<15 * 16 + 3, 15 * 16 + 3, 12 * 16 + 4>;
 
 template <typename T>
 static void wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
