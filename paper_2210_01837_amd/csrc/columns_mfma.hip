@@ -833,22 +833,26 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
     }
 
     // --- inverse transform to the band nodes ---------------------------------------
-    // vectors: U, W, T and, for the vorticity, (1/2)(k W + U') and -(1/2) T'
-    // (in the units of U)
+    // vectors: U, W, T and, for the vorticity, (1/2)(k W + U') and -(1/2) T', out
+    // of their units and scaled for the output while still in FP64: the factors
+    // go with the fourth power of a length and 1 / eta (1e36 H^2 / (Nx Ny eta) in
+    // the mean flow, whose k is a stand-in), beyond FP32 for legal boxes
     constexpr int kV = WOUT ? 5 : 3;
+    const double su = cp.scale * cUW, sw = su * cUW;   // (scale holds 1 / eta)
     D cf[kV][NA];
     if constexpr (WOUT) {
-      derivative<NA, D>(fresh(tabs, toff), U, up, xaddr, s2H, cf[3]);   // (1/2)(4/H)
-      derivative<NA, D>(fresh(tabs, toff), Y, up, xaddr, -s2H, cf[4]);
-      const double hw = 0.5 * k * cUW;
+      const double sd = s2H * su;                      // (1/2)(4/H)
+      derivative<NA, D>(fresh(tabs, toff), U, up, xaddr, sd, cf[3]);
+      derivative<NA, D>(fresh(tabs, toff), Y, up, xaddr, -sd, cf[4]);
+      const double hw = 0.5 * k * sw;
 #pragma unroll
       for (int i = 0; i < NA; ++i) cf[3][i] += (D)(hw * W[i]);
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      cf[0][i] = (D)U[i];
-      cf[1][i] = (D)W[i];
-      cf[2][i] = (D)Y[i];
+      cf[0][i] = (D)(su * U[i]);
+      cf[1][i] = (D)(sw * W[i]);
+      cf[2][i] = (D)(su * Y[i]);
     }
 #pragma unroll
     for (int v = 0; v < kV; ++v)
@@ -859,8 +863,7 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
       fetch(w, grp + stride, s_lo, true, true);
       __builtin_amdgcn_sched_barrier(0);
     }
-    const double su = cp.scale * cUW;               // (scale holds 1 / eta)
-    const D sw = (D)(su * cUW), ox = (D)(su * cx), oy = (D)(su * cy), hk = (D)(0.5 * k * su);
+    const D ox = (D)cx, oy = (D)cy, hk = (D)(0.5 * k);
     auto store = [&](int c, const D (&re)[kV], const D (&im)[kV]) {
       if (c <= hi && valid) {
         C* dst = out + (size_t)c * PS + idx;
@@ -874,7 +877,7 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
         const D lr = im[0], li = -re[0], tr = re[2], ti = im[2];
         put(0, fma(ox, lr, -(oy * tr)), fma(ox, li, -(oy * ti)));
         put(1, fma(oy, lr, ox * tr), fma(oy, li, ox * ti));
-        put(2, sw * re[1], sw * im[1]);
+        put(2, re[1], im[1]);
         if constexpr (WOUT) {
           const D qr = im[3], qi = -re[3], pr = re[4], pim = im[4];
           put(3, fma(ox, pr, -(oy * qr)), fma(ox, pim, -(oy * qi)));
