@@ -231,7 +231,8 @@ int fcmdp_stage_times(fcmdp_solver* s, double ms[8], int64_t* napplies);
  * different parallel decomposition and exist for cross-checks and tuning.
  * value: 0/1 for the switches; for the FFT row counts a power of two, or 12
  * for the x pass (rows per workgroup of the x and y passes, 0 = default: by
- * the row's length), rejected with FCMDP_EINVAL if the rows do not fit in LDS;
+ * the row's length; small FP64 grids on the kernels of GENERIC_FFT), rejected
+ * with FCMDP_EINVAL if the rows do not fit in LDS;
  * for the spread's workgroups 1..65535, block rows 8 or 16 and block order
  * 1 or 2 (0 = default), else FCMDP_EINVAL.
  * Not thread safe with respect to applies on the same solver.

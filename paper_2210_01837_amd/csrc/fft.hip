@@ -825,8 +825,8 @@ static DftOff dft_offsets(const fcmdp_solver* s) {
   return doff;
 }
 
-// Passes with workgroup-owned rows, two buffers and radices up to 8 (a
-// cross-check: variant FCMDP_VARIANT_GENERIC_FFT).
+// Passes with workgroup-owned rows, two buffers and radices up to 8: small FP64
+// grids, and a cross-check (variant FCMDP_VARIANT_GENERIC_FFT).
 template <typename T>
 static void generic_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                       const DftOff& doff, hipStream_t st) {
@@ -860,12 +860,27 @@ static void generic_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& 
                      (C*)spec, (const C*)s->tw_y, s->dftc, doff, rows, sign);
 }
 
-// One pass: the fixed plan of the length where there is one, else the run-time
-// plan of fft_rows.hip.
+// FP64 grids of at most 1600 KiB a channel with short rows take the two-buffer
+// kernels: small code and 256 threads for few points, where a launch of
+// fft_rows.hip is all latency.  Forward + inverse in us, fft_rows against these:
+// 24^2 x 32 planes 29 / 25, 64^2 x 32 44 / 38, 128^2 x 8 49 / 44, 80^2 x 32 47 /
+// 43 (at the line); beyond it 90^2 x 32 51 / 51 to 61 / 66, 32 x 180 x 32 47 / 56
+// to 63 / 96, 400 x 64 x 8 51 / 55.  Not in FP32, where their smaller radices
+// round more (an apply at 90^2: 6.6e-7 against 6.1e-7 from 64 bits).  Rows per
+// workgroup that a caller asks for are those of fft_rows.
+static bool small_grid(const fcmdp_solver* s) {
+  const DevParams& dp = s->dp;
+  const size_t channel = sizeof(double) * (size_t)dp.Nz * dp.Ny * dp.Nx;
+  return !s->mixed && channel <= 1600 * 1024 && dp.Nx <= 320 && dp.Ny <= 128 &&
+         s->rows_x == 0 && s->rows_y == 0;
+}
+
+// One pass: the fixed plan of the length where there is one, else the two-buffer
+// kernels or the run-time plan of fft_rows.hip.
 static hipError_t x_pass(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                          hipStream_t st) {
   const DftOff doff = dft_offsets(s);
-  if (s->force_generic_fft) {
+  if (s->force_generic_fft || small_grid(s)) {
     if (s->mixed) generic_x<float>(fwd, s, nch, in, out, doff, st);
     else generic_x<double>(fwd, s, nch, in, out, doff, st);
   } else if (s->codelet_x >= 0) {
@@ -877,7 +892,7 @@ static hipError_t x_pass(bool fwd, const fcmdp_solver* s, int nch, const void* i
 }
 static hipError_t y_pass(const fcmdp_solver* s, int nch, void* spec, int sign, hipStream_t st) {
   const DftOff doff = dft_offsets(s);
-  if (s->force_generic_fft) {
+  if (s->force_generic_fft || small_grid(s)) {
     if (s->mixed) generic_y<float>(s, nch, spec, doff, (float)sign, st);
     else generic_y<double>(s, nch, spec, doff, (double)sign, st);
   } else if (s->codelet_y >= 0) {
