@@ -268,12 +268,16 @@ enum {
                                         2 neighbouring strips side by side;
                                         0 = default: 1 if grid rows are whole
                                         128-byte lines, else 2 */
-  FCMDP_VARIANT_HALO_INTERP = 14     /* interpolation by workgroups that own
+  FCMDP_VARIANT_HALO_INTERP = 14,    /* interpolation by workgroups that own
                                         the particles of 26 x 26 cells and
                                         stage their planes with a 3-node halo,
                                         instead of partial sums over aligned
                                         32 x 16 tiles (read once) added per
                                         particle in a fixed order */
+  FCMDP_VARIANT_LARGE_CALL = 15      /* however few particles: the general sort
+                                        and the interpolation tiles of large
+                                        calls instead of one workgroup's sort
+                                        and one wavefront per particle */
 };
 int fcmdp_set_variant(fcmdp_solver* s, int key, int value);
 

@@ -808,6 +808,9 @@ int fcmdp_set_variant(fcmdp_solver* s, int key, int value) {
     case FCMDP_VARIANT_HALO_INTERP:
       s->force_halo_interp = on;
       return FCMDP_OK;
+    case FCMDP_VARIANT_LARGE_CALL:
+      s->force_large_call = on;
+      return FCMDP_OK;
     case FCMDP_VARIANT_SPREAD_ORDER:
       if (value < 0 || value > 2) return FCMDP_EINVAL;
       s->spread_order = value;

@@ -167,6 +167,8 @@ struct fcmdp_solver {
   // home-particle interpolation tiles with a staged halo instead of the
   // partial sums over aligned tiles
   bool force_halo_interp = false;
+  // the sort and the interpolation of large calls for few particles too (tests)
+  bool force_large_call = false;
   // use the untiled gather spread (tests)
   bool force_simple_spread = false;
   // use the per-patch gather spread instead of the matrix-core spread (tests),

@@ -450,7 +450,7 @@ __device__ __forceinline__ void cell_starts(int block, int n, int ncells,
 // Keys, band and domain errors of all particles, then the sort (keyA, valA).
 template <typename Tin>
 static void sort_impl(const fcmdp_solver* s, int n, const Tin* pos, hipStream_t st) {
-  if (n > 0 && n <= kSmallSort) {
+  if (n > 0 && n <= kSmallSort && !s->force_large_call) {
     hipLaunchKernelGGL(k_small_sort<Tin>, dim3(1), dim3(1024), 0, st, s->dp, n, pos, s->zc,
                        s->keyA, s->valA, s->band, s->nbad, s->key_passes);
   } else {

@@ -1006,7 +1006,8 @@ constexpr int kWaveInterp = 8192;
 hipError_t launch_interp(const fcmdp_solver* s, int n, const void* grid,
                          void* U, void* Omega, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  if (!s->force_simple_interp && !s->force_halo_interp && n <= kWaveInterp)
+  if (!s->force_simple_interp && !s->force_halo_interp && !s->force_large_call &&
+      n <= kWaveInterp)
     return launch_interp_wave(s, n, grid, U, Omega, st);
   if ((!s->force_simple_interp || s->dp.dt_omega) && !s->force_halo_interp &&
       interp_part_fits(s, n))
