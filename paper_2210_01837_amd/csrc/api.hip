@@ -166,6 +166,14 @@ int validate(const fcmdp_params* p) {
   const size_t csz = p->precision == FCMDP_MIXED ? 8 : 16;
   if (2 * (size_t)p->Ny * csz > fcmdp::kLdsBudget) return FCMDP_EINVAL;
   if ((size_t)(p->Nx + 1) * csz > fcmdp::kLdsBudget) return FCMDP_EINVAL;
+  // and a run-time plan whose stages fit a workgroup (no size that came this far
+  // is without one: tests/test_row_plans.py)
+  const bool fp32 = p->precision == FCMDP_MIXED;
+  for (int n : {p->Nx / 2, p->Ny}) {
+    fcmdp::RowPlan pl;
+    if (!fcmdp::make_row_plan(n, fp32, &pl) || !fcmdp::row_plan_fits(pl, fp32))
+      return FCMDP_EINVAL;
+  }
   return FCMDP_OK;
 }
 
