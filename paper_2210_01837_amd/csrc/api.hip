@@ -199,6 +199,8 @@ struct Sizes {
   size_t psi64, fzlo, lowk_part, lowk_coef, lowk_ex, lowk_ey;
   // torques through the kernel derivative, 0 when off
   size_t pdw, dpsi;
+  // root tables of the transforms and stage twiddles of the row plans
+  size_t rows;
 };
 
 // Truncation point t* of the dipole kernel's derivative: with r = t/alpha
@@ -249,6 +251,7 @@ Sizes sizes_for(const fcmdp_params* p, int64_t cap, int ZW) {
   s.hist = (256 * nblk + 256) * 4;   // block histograms + digit totals
   s.cells = ((size_t)p->Nx * p->Ny + 1) * 4;
   s.pinfo = c * 16;
+  s.rows = 2 * T * (2 * nkx + p->Ny + (size_t)p->Nx / 2 + p->Ny);
   s.pw = c * 32 * T;
   s.pf = c * 8 * T;
   // dense folded z weights [cap][2][Nz], padded for chunked readers that may
@@ -390,7 +393,7 @@ int fcmdp_workspace_bytes(const fcmdp_params* p, int64_t n, size_t* bytes) {
   const Sizes s = sizes_for(p, n, z_window_slots(p->Nz, p->H, alpha));
   *bytes = s.grid + s.spec + 2 * s.keys + 2 * s.vals + s.hist + s.cells +
            s.pinfo + s.pw + s.pf + s.psi + s.psi64 + s.fzlo + s.lowk_part +
-           s.lowk_coef + s.lowk_ex + s.lowk_ey + s.pdw + s.dpsi +
+           s.lowk_coef + s.lowk_ex + s.lowk_ey + s.pdw + s.dpsi + s.rows +
            (size_t)p->Nz * p->Nz * 16 + 65536;
   return FCMDP_OK;
 }
