@@ -833,26 +833,30 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
     }
 
     // --- inverse transform to the band nodes ---------------------------------------
-    // vectors: U, W, T and, for the vorticity, (1/2)(k W + U') and -(1/2) T', out
-    // of their units and scaled for the output while still in FP64: the factors
-    // go with the fourth power of a length and 1 / eta (1e36 H^2 / (Nx Ny eta) in
-    // the mean flow, whose k is a stand-in), beyond FP32 for legal boxes
+    // vectors: U, W, T and, for the vorticity, (1/2)(k W + U') and -(1/2) T'.  With
+    // FP32 transforms they leave their units and take the output's scale here, in
+    // FP64: the factors go with the fourth power of a length and 1 / eta (1e36 H^2
+    // / (Nx Ny eta) in the mean flow, whose k is a stand-in), beyond FP32 for legal
+    // boxes.  With FP64 transforms the nodes take them: 64 nodes, one wall, 303 us
+    // at 256^2 against 345 (more registers spilled).
     constexpr int kV = WOUT ? 5 : 3;
+    constexpr bool kCoef = sizeof(D) == 4;
     const double su = cp.scale * cUW, sw = su * cUW;   // (scale holds 1 / eta)
+    const double au = kCoef ? su : 1.0, aw = kCoef ? sw : 1.0;
     D cf[kV][NA];
     if constexpr (WOUT) {
-      const double sd = s2H * su;                      // (1/2)(4/H)
+      const double sd = s2H * au;                      // (1/2)(4/H)
       derivative<NA, D>(fresh(tabs, toff), U, up, xaddr, sd, cf[3]);
       derivative<NA, D>(fresh(tabs, toff), Y, up, xaddr, -sd, cf[4]);
-      const double hw = 0.5 * k * sw;
+      const double hw = 0.5 * k * (kCoef ? sw : cUW);
 #pragma unroll
       for (int i = 0; i < NA; ++i) cf[3][i] += (D)(hw * W[i]);
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      cf[0][i] = (D)(su * U[i]);
-      cf[1][i] = (D)(sw * W[i]);
-      cf[2][i] = (D)(su * Y[i]);
+      cf[0][i] = (D)(au * U[i]);
+      cf[1][i] = (D)(aw * W[i]);
+      cf[2][i] = (D)(au * Y[i]);
     }
 #pragma unroll
     for (int v = 0; v < kV; ++v)
@@ -863,7 +867,9 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
       fetch(w, grp + stride, s_lo, true, true);
       __builtin_amdgcn_sched_barrier(0);
     }
-    const D ox = (D)cx, oy = (D)cy, hk = (D)(0.5 * k);
+    const double nu = kCoef ? 1.0 : su;
+    const D nw = kCoef ? D(1) : (D)sw;
+    const D ox = (D)(nu * cx), oy = (D)(nu * cy), hk = (D)(0.5 * k * nu);
     auto store = [&](int c, const D (&re)[kV], const D (&im)[kV]) {
       if (c <= hi && valid) {
         C* dst = out + (size_t)c * PS + idx;
@@ -877,7 +883,7 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
         const D lr = im[0], li = -re[0], tr = re[2], ti = im[2];
         put(0, fma(ox, lr, -(oy * tr)), fma(ox, li, -(oy * ti)));
         put(1, fma(oy, lr, ox * tr), fma(oy, li, ox * ti));
-        put(2, re[1], im[1]);
+        put(2, nw * re[1], nw * im[1]);
         if constexpr (WOUT) {
           const D qr = im[3], qi = -re[3], pr = re[4], pim = im[4];
           put(3, fma(ox, pr, -(oy * qr)), fma(ox, pim, -(oy * qi)));

@@ -76,3 +76,18 @@ def test_change_of_units(length, visc, geometry):
     other = Box(geometry, 24.0 * a, 20.0 * a, 9.0 * a, 48, 40, 24, eta=b)
     V, Nu = _run(other, "mixed", pos * a, F, T * a)
     assert rel_err(V * (a * b), U) < 1e-6 and rel_err(Nu * (a * a * b), Om) < 1e-6
+
+
+@pytest.mark.parametrize("geometry", ["bw", "sc"])
+@pytest.mark.parametrize("name", ["water_um", "nm", "nm_thin"])
+def test_units_with_many_nodes(name, geometry):
+    """Nz > 32: FP64 transforms of FP32 data."""
+    h, H, n, eta, force = UNITS[name]
+    box = Box(geometry, n * h, n * h, H, n, n, 40, eta=eta)
+    pos, F, T = _particles(box, 40, 73, "mixed")
+    F = (F * force).astype(np.float32).astype(np.float64)
+    T = (T * (force * h)).astype(np.float32).astype(np.float64)
+    print(f"[units, 40 nodes] {name} {geometry}", flush=True)
+    U, Om = _run(box, "mixed", pos, F, T)
+    rU, rO = oracle_apply(box, pos, F, T)
+    assert rel_err(U, rU) < 1e-5 and rel_err(Om, rO) < 1e-5
