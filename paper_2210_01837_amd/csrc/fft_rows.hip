@@ -356,9 +356,15 @@ static hipError_t rows_x(bool fwd, const fcmdp_solver* s, int nch, const void* i
   // workgroups to hide the barriers of each other.  Forward / inverse in us,
   // full against half: 1176 points FP32 578/495 -> 565/476, 756 FP32 246/191 ->
   // 219/173, 768 FP64 758/742 -> 738/677; with seven batches already there
-  // (360 FP32) 109/81 -> 112/82.  Fewer rows also if LDS or threads run out.
+  // (360 FP32) 109/81 -> 112/82.  In FP32 not where one full batch fits: the two
+  // half ones are slower at 30 of 33 lengths from 1280 to 2548 (1280^2, 8 planes
+  // 563/841 against 668/941, 2000^2 1376/2089 against 1546/2230; the others lose
+  // 1 to 3% full: 1632, 2268, 2500).  In FP64 the two are even there (1500^2 15%
+  // for full, 2160^2 8% for half).  Fewer rows also if LDS or threads run out.
   const int line = fp32 ? 16 : 8;
-  int rows = s->rows_x > 0 ? s->rows_x : 4 * line * row > kLdsBudget ? line / 2 : line, nt = 0;
+  const size_t full = line * row;
+  const bool half = 4 * full > kLdsBudget && (!fp32 || 2 * full <= kLdsBudget);
+  int rows = s->rows_x > 0 ? s->rows_x : half ? line / 2 : line, nt = 0;
   for (;; rows = rows == 12 ? 8 : rows / 2) {
     nt = rows * row <= kLdsBudget ? row_threads(pl, rows, rows * row, fp32) : 0;
     if (nt || rows == 1) break;

@@ -1,6 +1,7 @@
 """xy transforms of small grids: the two-buffer kernels that they take by default
 in FP64 up to the lines of that rule and just beyond it, and the row kernels at the
-same sizes (rows per workgroup asked for), every radix of their run-time plans.
+same sizes (rows per workgroup asked for), every radix of their run-time plans; and
+rows so long that one full batch of them fits a CU, whole and ragged batches.
 
 Tolerances as for the other row transforms, FP64 1e-14, FP32 2e-6."""
 import numpy as np
@@ -63,3 +64,10 @@ def test_row_kernels_at_small_sizes(nx, ny, full, precision):
     print(f"[small row transforms] {nx}x{ny} {precision} full {full}", flush=True)
     rows = (16 if precision == "mixed" else 8, 8) if full else (1, 1)
     _check(nx, ny, 8, 5, 6, precision, rows)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nx,ny", [(1274, 24), (1280, 32), (1320, 26), (2520, 22), (2592, 20)])
+def test_long_rows(nx, ny, precision):
+    print(f"[long rows] {nx}x{ny} {precision}", flush=True)
+    _check(nx, ny, 8, 4, 5, precision)
