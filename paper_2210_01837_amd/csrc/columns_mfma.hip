@@ -405,9 +405,9 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
   const double l0 = dp.slip0, lH = GEOM == 1 ? dp.slipH : 0.0;
   const bool slip = l0 != 0.0 || lH != 0.0;        // uniform
   const int s_lo = lo / 4, s_hi = hi / 4;
-  // the first steps of a group's band values are loaded while the inverse
-  // transform of the group before it runs (FP32 transforms: the registers are
-  // there)
+  // a group's band values are loaded several steps ahead of their products; the
+  // next group's during this one's inverse transform do not fit the registers
+  // (80 spilled, 1.85 -> 2.60 ms at 2176^2)
   constexpr int kCh = 5;                           // steps in flight
   // (part L takes all but G_z, part T all but F_z)
   auto fetch = [&](C (&w)[kCh][kNin], int grp, int s0, bool part_l, bool part_t) {
@@ -430,7 +430,6 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
   // route's registers do not weigh on the other groups)
   auto run = [&](auto low_tag) __attribute__((always_inline)) {
   constexpr bool LOW = decltype(low_tag)::value;
-  constexpr bool kAhead = sizeof(D) == 4 && !LOW && false;
   const int ns = dp.lowk_ns;
   int grp, stride, last;
   if constexpr (LOW) {
@@ -449,7 +448,6 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
     last = G;
   }
   C w[kCh][kNin];
-  if (kAhead && grp < last) fetch(w, grp, s_lo, true, true);
   for (; grp < last; grp += stride) {
     int ln = lane;                                 // (opaque, as in fresh())
     asm volatile("" : "+v"(ln));
@@ -474,10 +472,7 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
     int lcol = -1;
     if constexpr (kLow) {
       lcol = nyq || !valid ? -1 : lowk_col(dp, kxi, nyi);
-      if ((__any(lcol >= 0) != 0) != LOW) {
-        if (kAhead && grp + stride < last) fetch(w, grp + stride, s_lo, true, true);
-        continue;
-      }
+      if ((__any(lcol >= 0) != 0) != LOW) continue;
     }
 
     // --- forward transform of the band nodes ---------------------------------
@@ -496,7 +491,7 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
       const D dcx = (D)cx, dcy = (D)cy, hk = (D)(0.5 * k);
       const D hcx = (D)(0.5 * cx), hcy = (D)(0.5 * cy);
       for (int s0 = s_lo; s0 <= s_hi; s0 += kCh) {
-        if (!kAhead || s0 > s_lo) fetch(w, grp, s0, PL, PT);
+        fetch(w, grp, s0, PL, PT);
 #pragma unroll
         for (int u = 0; u < kCh; ++u) {
           if (s0 + u > s_hi) break;                 // uniform
@@ -862,11 +857,6 @@ k_columns_mfma(ColParams cp, int low_blocks, const int* __restrict__ band,
     for (int v = 0; v < kV; ++v)
 #pragma unroll
       for (int j = 0; j < kHalf; ++j) swap16(cf[v][j], cf[v][kHalf + j]);
-    if (kAhead && grp + stride < last) {
-      __builtin_amdgcn_sched_barrier(0);
-      fetch(w, grp + stride, s_lo, true, true);
-      __builtin_amdgcn_sched_barrier(0);
-    }
     const double nu = kCoef ? 1.0 : su;
     const D nw = kCoef ? D(1) : (D)sw;
     const D ox = (D)(nu * cx), oy = (D)(nu * cy), hk = (D)(0.5 * k * nu);

@@ -194,26 +194,18 @@ k_fft_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
 }
 
 // ---- row-owned in-place transforms ------------------------------------------
-// TPR threads (one to four wavefronts) own one row in LDS.  A Stockham stage
-// first reads every butterfly input of the thread into registers and then
-// writes the outputs back in place.  Butterfly j of a stage belongs to thread
-// j mod TPR, so the loop trip counts are uniform and there are no index
-// divisions by the row count.  With TPR = 64 the row is private to one
-// wavefront, whose LDS accesses complete in issue order, and stages need no
-// workgroup barrier; with more threads per row all rows of the workgroup
-// step through the (identical) stage sequence together.
-
+// One wavefront owns one row in LDS.  A Stockham stage first reads every
+// butterfly input of the lane into registers and then writes the outputs back in
+// place.  Butterfly j of a stage belongs to lane j mod 64, so the loop trip counts
+// are uniform and there are no index divisions by the row count; the row is
+// private to its wavefront, whose LDS accesses complete in issue order, and
+// stages need no workgroup barrier.
+constexpr int kLanes = 64;
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <int TPR>
-__device__ __forceinline__ void row_sync() {
-  if constexpr (TPR == 64) wave_sync();
-  else __syncthreads();
 }
 
 // ---- fixed plans ("codelets") ----------------------------------------------
@@ -314,8 +306,7 @@ struct CodeletLayout {
 
 // One stage of a fixed plan: every size is a compile-time constant, inputs
 // in layout LI, outputs in layout LO.
-template <typename T, int R, int TPR, int NB, int N, int NS, int BI, int PI, int BO,
-          int PO>
+template <typename T, int R, int NB, int N, int NS, int BI, int PI, int BO, int PO>
 __device__ __forceinline__ void stage_fixed(cplx_t<T>* row, int t,
                                             const cplx_t<T>* __restrict__ tw,
                                             const T* __restrict__ cs, T sign) {
@@ -331,17 +322,17 @@ __device__ __forceinline__ void stage_fixed(cplx_t<T>* row, int t,
   C v[NB][R];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int j = t + TPR * i;
+    const int j = t + kLanes * i;
     if (j < nb) {
       const int base = (int)((unsigned)j / BI) * PI + j;
 #pragma unroll
       for (int q = 0; q < R; ++q) v[i][q] = row[base + q * rstep];
     }
   }
-  row_sync<TPR>();
+  wave_sync();
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int j = t + TPR * i;
+    const int j = t + kLanes * i;
     if (j < nb) {
       C* x = v[i];
       const int k = j % NS;
@@ -360,32 +351,32 @@ __device__ __forceinline__ void stage_fixed(cplx_t<T>* row, int t,
       for (int q = 0; q < R; ++q) row[base + q * wstep] = x[q];
     }
   }
-  row_sync<TPR>();
+  wave_sync();
 }
 
-template <typename T, int TPR, typename Lay, int S, int NS, int Code, int... Rest>
+template <typename T, typename Lay, int S, int NS, int Code, int... Rest>
 __device__ __forceinline__ void run_codes(cplx_t<T>* row, int t,
                                           const cplx_t<T>* __restrict__ tw,
                                           const T* __restrict__ dftc,
                                           const DftOff& doff, T sign) {
   constexpr int R = Code >> 4, NB = Code & 15;
   constexpr RowLay LI = Lay::kTable.lay[S], LO = Lay::kTable.lay[S + 1];
-  stage_fixed<T, R, TPR, NB, Lay::kN, NS, LI.B, LI.pad, LO.B, LO.pad>(
-      row, t, tw, dftc + doff.off[R], sign);
+  stage_fixed<T, R, NB, Lay::kN, NS, LI.B, LI.pad, LO.B, LO.pad>(row, t, tw, dftc + doff.off[R],
+                                                                  sign);
   if constexpr (sizeof...(Rest) > 0)
-    run_codes<T, TPR, Lay, S + 1, NS * R, Rest...>(row, t, tw, dftc, doff, sign);
+    run_codes<T, Lay, S + 1, NS * R, Rest...>(row, t, tw, dftc, doff, sign);
 }
 
 template <int... Codes>
 struct FixedRows {
   using Lay = CodeletLayout<Codes...>;
   static constexpr int kN = Lay::kN;                // transform length
-  template <typename T, int TPR>
-  __device__ __forceinline__ static void run(cplx_t<T>* row, int, const FFTPlan&, int t,
+  template <typename T>
+  __device__ __forceinline__ static void run(cplx_t<T>* row, int t,
                              const cplx_t<T>* __restrict__ tw,
                              const T* __restrict__ dftc, const DftOff& doff,
                              T sign) {
-    run_codes<T, TPR, Lay, 0, 1, Codes...>(row, t, tw, dftc, doff, sign);
+    run_codes<T, Lay, 0, 1, Codes...>(row, t, tw, dftc, doff, sign);
   }
   __host__ __device__ static constexpr int span(int n) {
     return n > Lay::kTable.span ? n : Lay::kTable.span;
@@ -401,12 +392,11 @@ __host__ __device__ constexpr int x_stride(int M) {
 
 // x-pass, real rows -> half spectrum, ROWS rows per workgroup, written
 // transposed as ROWS-long runs of consecutive y.
-template <typename T, int ROWS, int TPR, typename Run>
-__global__ void __launch_bounds__(ROWS * TPR)
-k_fftw_x_r2c(DevParams dp, FFTPlan plan, const int* __restrict__ band,
-             const T* __restrict__ grid, cplx_t<T>* __restrict__ spec,
-             const cplx_t<T>* __restrict__ tw, const cplx_t<T>* __restrict__ rtw,
-             const T* __restrict__ dftc, DftOff doff) {
+template <typename T, int ROWS, typename Run>
+__global__ void __launch_bounds__(ROWS * kLanes)
+k_fftw_x_r2c(DevParams dp, const int* __restrict__ band, const T* __restrict__ grid,
+             cplx_t<T>* __restrict__ spec, const cplx_t<T>* __restrict__ tw,
+             const cplx_t<T>* __restrict__ rtw, const T* __restrict__ dftc, DftOff doff) {
   using C = cplx_t<T>;
   extern __shared__ unsigned char lds_raw[];
   C* lds = reinterpret_cast<C*>(lds_raw);
@@ -417,17 +407,17 @@ k_fftw_x_r2c(DevParams dp, FFTPlan plan, const int* __restrict__ band,
   if (c < band[0] || c > band[1]) return;           // whole workgroup
   const int y0 = blockIdx.x * ROWS;
   const int nr = min(ROWS, dp.Ny - y0);
-  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);
-  const int t = threadIdx.x % TPR;
+  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int t = threadIdx.x % kLanes;
   C* row = lds + wr * S;
   // rows past the grid edge (tail workgroup) transform a copy of row y0
   const int y = wr < nr ? y0 + wr : y0;
   const C* src = reinterpret_cast<const C*>(grid + ((size_t)p * dp.Ny + y) * dp.Nx);
 #pragma unroll 4
-  for (int i = t; i < M; i += TPR) row[i] = src[i];
-  row_sync<TPR>();
-  Run::template run<T, TPR>(row, M, plan, t, tw, dftc, doff, T(-1));
-  for (int k = t; k <= M / 2; k += TPR) {
+  for (int i = t; i < M; i += kLanes) row[i] = src[i];
+  wave_sync();
+  Run::template run<T>(row, t, tw, dftc, doff, T(-1));
+  for (int k = t; k <= M / 2; k += kLanes) {
     const C zk = row[k];
     if (k == 0) {
       row[0] = r2c_post(zk, zk, rtw[0]);
@@ -442,7 +432,7 @@ k_fftw_x_r2c(DevParams dp, FFTPlan plan, const int* __restrict__ band,
   const size_t pbase = (size_t)p * dp.Nkx * dp.Ny;
   if constexpr (ROWS % 2 == 0 && sizeof(T) == 4) {
     // two consecutive rows per thread: one 16-byte store (y0 and Ny even)
-    for (int idx = threadIdx.x; idx < (M + 1) * (ROWS / 2); idx += ROWS * TPR) {
+    for (int idx = threadIdx.x; idx < (M + 1) * (ROWS / 2); idx += ROWS * kLanes) {
       const int k = idx / (ROWS / 2);
       const int r = 2 * (idx % (ROWS / 2));
       C* dst = spec + pbase + (size_t)k * dp.Ny + y0 + r;
@@ -455,7 +445,7 @@ k_fftw_x_r2c(DevParams dp, FFTPlan plan, const int* __restrict__ band,
       }
     }
   } else {
-    for (int idx = threadIdx.x; idx < (M + 1) * ROWS; idx += ROWS * TPR) {
+    for (int idx = threadIdx.x; idx < (M + 1) * ROWS; idx += ROWS * kLanes) {
       const int k = idx / ROWS;
       const int r = idx % ROWS;
       if (r < nr) spec[pbase + (size_t)k * dp.Ny + y0 + r] = lds[r * S + k];
@@ -464,32 +454,29 @@ k_fftw_x_r2c(DevParams dp, FFTPlan plan, const int* __restrict__ band,
 }
 
 // y-pass, in place on contiguous rows of length Ny.
-template <typename T, int ROWS, int TPR, typename Run>
-__global__ void __launch_bounds__(ROWS * TPR)
-k_fftw_y(DevParams dp, FFTPlan plan, const int* __restrict__ band,
-         cplx_t<T>* __restrict__ spec, const cplx_t<T>* __restrict__ tw,
+template <typename T, int ROWS, typename Run>
+__global__ void __launch_bounds__(ROWS * kLanes)
+k_fftw_y(DevParams dp, const int* __restrict__ band, cplx_t<T>* __restrict__ spec,
+         const cplx_t<T>* __restrict__ tw,
          const T* __restrict__ dftc, DftOff doff, T sign) {
   using C = cplx_t<T>;
   extern __shared__ unsigned char lds_raw[];
   const int p = blockIdx.y;
   const int c = p % dp.Nz;
   if (c < band[0] || c > band[1]) return;
-  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);
-  const int t = threadIdx.x % TPR;
+  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int t = threadIdx.x % kLanes;
   const int kx = blockIdx.x * ROWS + wr;
-  const bool live = kx < dp.Nkx;
-  if (TPR == 64 && !live) return;                   // a whole wavefront
+  if (kx >= dp.Nkx) return;                         // a whole wavefront
   const int N = dp.Ny;
   C* row = reinterpret_cast<C*>(lds_raw) + wr * Run::span(N);
-  C* g = spec + ((size_t)p * dp.Nkx + (live ? kx : 0)) * N;
+  C* g = spec + ((size_t)p * dp.Nkx + kx) * N;
 #pragma unroll 4
-  for (int i = t; i < N; i += TPR) row[i] = g[i];
-  row_sync<TPR>();
-  Run::template run<T, TPR>(row, N, plan, t, tw, dftc, doff, sign);
-  if (live) {
+  for (int i = t; i < N; i += kLanes) row[i] = g[i];
+  wave_sync();
+  Run::template run<T>(row, t, tw, dftc, doff, sign);
 #pragma unroll 4
-    for (int i = t; i < N; i += TPR) g[i] = row[i];
-  }
+  for (int i = t; i < N; i += kLanes) g[i] = row[i];
 }
 
 // y-pass as a persistent loop: workgroup g (one wavefront) transforms the
@@ -498,8 +485,8 @@ k_fftw_y(DevParams dp, FFTPlan plan, const int* __restrict__ band,
 // requests in flight through its arithmetic.  Fixed-length plans only.
 template <typename T, typename Run>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8)))
-k_fftw_y_pipe(DevParams dp, FFTPlan plan, const int* __restrict__ band,
-              cplx_t<T>* __restrict__ spec, const cplx_t<T>* __restrict__ tw,
+k_fftw_y_pipe(DevParams dp, const int* __restrict__ band, cplx_t<T>* __restrict__ spec,
+              const cplx_t<T>* __restrict__ tw,
               const T* __restrict__ dftc, DftOff doff, T sign, int nch) {
   using C = cplx_t<T>;
   constexpr int N = Run::kN;                        // == dp.Ny
@@ -546,7 +533,7 @@ k_fftw_y_pipe(DevParams dp, FFTPlan plan, const int* __restrict__ band,
     const T* csl = dftc;
     int tl = t;
     asm volatile("" : "+s"(twl), "+s"(csl), "+v"(tl));
-    Run::template run<T, 64>(row, N, plan, tl, twl, csl, doff, sign);
+    Run::template run<T>(row, tl, twl, csl, doff, sign);
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       if (t + 64 * i < N) g[t + 64 * i] = row[t + 64 * i];
@@ -556,12 +543,11 @@ k_fftw_y_pipe(DevParams dp, FFTPlan plan, const int* __restrict__ band,
 
 // x-pass, half spectrum -> real rows, reading ROWS-long runs of the
 // transposed layout.
-template <typename T, int ROWS, int TPR, typename Run>
-__global__ void __launch_bounds__(ROWS * TPR)
-k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
-             const cplx_t<T>* __restrict__ spec, T* __restrict__ grid,
-             const cplx_t<T>* __restrict__ tw, const cplx_t<T>* __restrict__ rtw,
-             const T* __restrict__ dftc, DftOff doff) {
+template <typename T, int ROWS, typename Run>
+__global__ void __launch_bounds__(ROWS * kLanes)
+k_fftw_x_c2r(DevParams dp, const int* __restrict__ band, const cplx_t<T>* __restrict__ spec,
+             T* __restrict__ grid, const cplx_t<T>* __restrict__ tw,
+             const cplx_t<T>* __restrict__ rtw, const T* __restrict__ dftc, DftOff doff) {
   using C = cplx_t<T>;
   extern __shared__ unsigned char lds_raw[];
   C* lds = reinterpret_cast<C*>(lds_raw);
@@ -580,18 +566,18 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
       // whole workgroup: a thread issues all of its loads (nine cover the
       // half spectrum of 2176-point rows) before the first LDS store
       constexpr int kB = 9;
-      for (int base = threadIdx.x; base < total; base += kB * ROWS * TPR) {
+      for (int base = threadIdx.x; base < total; base += kB * ROWS * kLanes) {
         float4 v[kB];
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
-          const int idx = min(base + u * ROWS * TPR, total - 1);   // in bounds
+          const int idx = min(base + u * ROWS * kLanes, total - 1);   // in bounds
           const int k = idx / (ROWS / 2);
           const int r = 2 * (idx % (ROWS / 2));
           v[u] = *reinterpret_cast<const float4*>(spec + pbase + (size_t)k * dp.Ny + y0 + r);
         }
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
-          const int idx = base + u * ROWS * TPR;
+          const int idx = base + u * ROWS * kLanes;
           if (idx < total) {
             const int k = idx / (ROWS / 2);
             const int r = 2 * (idx % (ROWS / 2));
@@ -601,7 +587,7 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
         }
       }
     } else {
-      for (int idx = threadIdx.x; idx < total; idx += ROWS * TPR) {
+      for (int idx = threadIdx.x; idx < total; idx += ROWS * kLanes) {
         const int k = idx / (ROWS / 2);
         const int r = 2 * (idx % (ROWS / 2));
         const C* src = spec + pbase + (size_t)k * dp.Ny + y0;
@@ -619,7 +605,7 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
       }
     }
   } else {
-    for (int idx = threadIdx.x; idx < (M + 1) * ROWS; idx += ROWS * TPR) {
+    for (int idx = threadIdx.x; idx < (M + 1) * ROWS; idx += ROWS * kLanes) {
       const int k = idx / ROWS;
       const int r = idx % ROWS;
       // rows past the grid edge transform a copy of row y0
@@ -627,10 +613,10 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
     }
   }
   __syncthreads();
-  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);
-  const int t = threadIdx.x % TPR;
+  const int wr = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int t = threadIdx.x % kLanes;
   C* row = lds + wr * S;
-  for (int k = t; k <= M / 2; k += TPR) {
+  for (int k = t; k <= M / 2; k += kLanes) {
     if (k == 0) {
       C x0 = row[0], xm = row[M];
       x0.y = T(0);
@@ -642,16 +628,16 @@ k_fftw_x_c2r(DevParams dp, FFTPlan plan, const int* __restrict__ band,
       if (M - k != k) row[M - k] = c2r_pre(xm, xk, rtw[M - k]);
     }
   }
-  row_sync<TPR>();
-  Run::template run<T, TPR>(row, M, plan, t, tw, dftc, doff, T(1));
+  wave_sync();
+  Run::template run<T>(row, t, tw, dftc, doff, T(1));
   if (wr < nr) {
     C* dst = reinterpret_cast<C*>(grid + ((size_t)p * dp.Ny + y0 + wr) * dp.Nx);
 #pragma unroll 4
-    for (int i = t; i < M; i += TPR) dst[i] = row[i];
+    for (int i = t; i < M; i += kLanes) dst[i] = row[i];
   }
 }
 
-template <typename T, int ROWS, int TPR, typename Run>
+template <typename T, int ROWS, typename Run>
 static void launch_wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* in,
                           void* out, const DftOff& doff, hipStream_t st) {
   using C = cplx_t<T>;
@@ -661,12 +647,12 @@ static void launch_wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* 
   dim3 g((dp.Ny + ROWS - 1) / ROWS, nch * dp.Nz);
   const T* cs = (const T*)s->dftc_t;
   if (fwd)
-    hipLaunchKernelGGL((k_fftw_x_r2c<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR),
-                       lds, st, dp, s->plan_x, s->band, (const T*)in, (C*)out,
+    hipLaunchKernelGGL((k_fftw_x_r2c<T, ROWS, Run>), g, dim3(ROWS * kLanes),
+                       lds, st, dp, s->band, (const T*)in, (C*)out,
                        (const C*)s->tw_x, (const C*)s->tw_r, cs, doff);
   else
-    hipLaunchKernelGGL((k_fftw_x_c2r<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR),
-                       lds, st, dp, s->plan_x, s->band, (const C*)in, (T*)out,
+    hipLaunchKernelGGL((k_fftw_x_c2r<T, ROWS, Run>), g, dim3(ROWS * kLanes),
+                       lds, st, dp, s->band, (const C*)in, (T*)out,
                        (const C*)s->tw_x, (const C*)s->tw_r, cs, doff);
 }
 
@@ -678,7 +664,7 @@ static int rows_fitting(size_t row_bytes, int maxrows) {
   while (r > 1 && (size_t)r * row_bytes > kLdsBudget) r /= 2;
   return r;
 }
-template <typename T, int TPR, typename Run>
+template <typename T, typename Run>
 static void wave_x_rows(bool fwd, const fcmdp_solver* s, int nch, const void* in,
                         void* out, const DftOff& doff, hipStream_t st) {
   const size_t row = (size_t)x_stride<Run>(s->dp.Nx / 2) * sizeof(cplx_t<T>);
@@ -688,36 +674,35 @@ static void wave_x_rows(bool fwd, const fcmdp_solver* s, int nch, const void* in
     if (r == 8 && 12 * row <= kLdsBudget) r = 12;
   }
   switch (r) {
-    case 16: launch_wave_x<T, 16, 64, Run>(fwd, s, nch, in, out, doff, st); break;
-    case 12: launch_wave_x<T, 12, 64, Run>(fwd, s, nch, in, out, doff, st); break;
-    case 8: launch_wave_x<T, 8, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
-    case 4: launch_wave_x<T, 4, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
-    case 2: launch_wave_x<T, 2, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
-    default: launch_wave_x<T, 1, TPR, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 16: launch_wave_x<T, 16, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 12: launch_wave_x<T, 12, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 8: launch_wave_x<T, 8, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 4: launch_wave_x<T, 4, Run>(fwd, s, nch, in, out, doff, st); break;
+    case 2: launch_wave_x<T, 2, Run>(fwd, s, nch, in, out, doff, st); break;
+    default: launch_wave_x<T, 1, Run>(fwd, s, nch, in, out, doff, st); break;
   }
 }
 
-template <typename T, int ROWS, int TPR, typename Run>
+template <typename T, int ROWS, typename Run>
 static void launch_wave_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                           T sign, hipStream_t st) {
   using C = cplx_t<T>;
   const DevParams& dp = s->dp;
   const size_t lds = (size_t)ROWS * Run::span(dp.Ny) * sizeof(C);
   dim3 g((dp.Nkx + ROWS - 1) / ROWS, nch * dp.Nz);
-  hipLaunchKernelGGL((k_fftw_y<T, ROWS, TPR, Run>), g, dim3(ROWS * TPR), lds, st,
-                     dp, s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
-                     (const T*)s->dftc_t, doff, sign);
+  hipLaunchKernelGGL((k_fftw_y<T, ROWS, Run>), g, dim3(ROWS * kLanes), lds, st,
+                     dp, s->band, (C*)spec, (const C*)s->tw_y, (const T*)s->dftc_t, doff, sign);
 }
 
-template <typename T, int TPR, typename Run>
+template <typename T, typename Run>
 static void wave_y_rows(const fcmdp_solver* s, int nch, void* spec, const DftOff& doff,
                         T sign, hipStream_t st) {
   // rows are independent; one per workgroup packs LDS best
   switch (s->rows_y) {
-    case 8: launch_wave_y<T, 8, TPR, Run>(s, nch, spec, doff, sign, st); break;
-    case 4: launch_wave_y<T, 4, TPR, Run>(s, nch, spec, doff, sign, st); break;
-    case 2: launch_wave_y<T, 2, TPR, Run>(s, nch, spec, doff, sign, st); break;
-    default: launch_wave_y<T, 1, TPR, Run>(s, nch, spec, doff, sign, st); break;
+    case 8: launch_wave_y<T, 8, Run>(s, nch, spec, doff, sign, st); break;
+    case 4: launch_wave_y<T, 4, Run>(s, nch, spec, doff, sign, st); break;
+    case 2: launch_wave_y<T, 2, Run>(s, nch, spec, doff, sign, st); break;
+    default: launch_wave_y<T, 1, Run>(s, nch, spec, doff, sign, st); break;
   }
 }
 
@@ -732,8 +717,7 @@ static void wave_y_pipe(const fcmdp_solver* s, int nch, void* spec, const DftOff
   const int per_cu = (int)std::min<size_t>(8, kLdsBudget / lds);
   const int g = std::max(1, s->num_cu) * std::max(1, per_cu);
   hipLaunchKernelGGL((k_fftw_y_pipe<T, Run>), dim3(g), dim3(64), lds, st, dp,
-                     s->plan_y, s->band, (C*)spec, (const C*)s->tw_y,
-                     (const T*)s->dftc_t, doff, sign,
+                     s->band, (C*)spec, (const C*)s->tw_y, (const T*)s->dftc_t, doff, sign,
                      nch);
 }
 
@@ -756,12 +740,12 @@ template <typename T>
 static void wave_x(bool fwd, const fcmdp_solver* s, int nch, const void* in, void* out,
                    const DftOff& doff, hipStream_t st) {
   switch (s->codelet_x) {
-    case 0: wave_x_rows<T, 64, Codelet0>(fwd, s, nch, in, out, doff, st); return;
-    case 1: wave_x_rows<T, 64, Codelet1>(fwd, s, nch, in, out, doff, st); return;
-    case 2: wave_x_rows<T, 64, Codelet2>(fwd, s, nch, in, out, doff, st); return;
-    case 3: wave_x_rows<T, 64, Codelet3>(fwd, s, nch, in, out, doff, st); return;
-    case 4: wave_x_rows<T, 64, Codelet4>(fwd, s, nch, in, out, doff, st); return;
-    case 5: wave_x_rows<T, 64, Codelet5>(fwd, s, nch, in, out, doff, st); return;
+    case 0: wave_x_rows<T, Codelet0>(fwd, s, nch, in, out, doff, st); return;
+    case 1: wave_x_rows<T, Codelet1>(fwd, s, nch, in, out, doff, st); return;
+    case 2: wave_x_rows<T, Codelet2>(fwd, s, nch, in, out, doff, st); return;
+    case 3: wave_x_rows<T, Codelet3>(fwd, s, nch, in, out, doff, st); return;
+    case 4: wave_x_rows<T, Codelet4>(fwd, s, nch, in, out, doff, st); return;
+    case 5: wave_x_rows<T, Codelet5>(fwd, s, nch, in, out, doff, st); return;
     default: break;
   }
 }
@@ -781,12 +765,12 @@ static void wave_y(const fcmdp_solver* s, int nch, void* spec, const DftOff& dof
     }
   }
   switch (s->codelet_y) {
-    case 0: wave_y_rows<T, 64, Codelet0>(s, nch, spec, doff, sign, st); return;
-    case 1: wave_y_rows<T, 64, Codelet1>(s, nch, spec, doff, sign, st); return;
-    case 2: wave_y_rows<T, 64, Codelet2>(s, nch, spec, doff, sign, st); return;
-    case 3: wave_y_rows<T, 64, Codelet3>(s, nch, spec, doff, sign, st); return;
-    case 4: wave_y_rows<T, 64, Codelet4>(s, nch, spec, doff, sign, st); return;
-    case 5: wave_y_rows<T, 64, Codelet5>(s, nch, spec, doff, sign, st); return;
+    case 0: wave_y_rows<T, Codelet0>(s, nch, spec, doff, sign, st); return;
+    case 1: wave_y_rows<T, Codelet1>(s, nch, spec, doff, sign, st); return;
+    case 2: wave_y_rows<T, Codelet2>(s, nch, spec, doff, sign, st); return;
+    case 3: wave_y_rows<T, Codelet3>(s, nch, spec, doff, sign, st); return;
+    case 4: wave_y_rows<T, Codelet4>(s, nch, spec, doff, sign, st); return;
+    case 5: wave_y_rows<T, Codelet5>(s, nch, spec, doff, sign, st); return;
     default: break;
   }
 }
