@@ -35,13 +35,16 @@
 // z-derivatives on the right-hand sides are taken through B^2 D = B, i.e.
 // (f_{m-1} - f_{m+1}) / (2 m): no recurrence over the coefficients.
 //
-// Bound by several units at once, at two wavefronts per SIMD (256 registers, none
-// spilled): vector issue 0.43 (the FP64 sweeps), matrix cores 0.28, HBM 0.64 of a
-// plain copy at 2176^2, 20 planes.  Against eight lanes per column with segmented
-// scans (and, for FP64 data or Nz > 32, one thread per column in scratch), one
-// launch: 2176^2, 20 planes, mixed 3.37 -> 1.62 ms; two walls 4.39 -> 1.9;
-// 2700^2, 11 planes, forces only 3.34 -> 1.05; 768^2 0.43 -> 0.22; in FP64 1.41 ->
-// 0.44; 192^2, Nz = 48, FP64 6.2 -> 0.12.
+// Bound by several units at once, at two wavefronts per SIMD: vector issue 0.43
+// (the FP64 sweeps), matrix cores 0.28, HBM 0.64 of a plain copy at 2176^2, 20
+// planes.  Registers, as the compiler reports them for FP32 transforms: none
+// spilled up to 20 nodes, up to 32 nodes at most 6 above one wall and 89 to 119
+// between two, where the FP64 low-wavenumber copy shares the kernel; for FP64
+// transforms at most 6 up to 48 nodes, up to 163 beyond.  Against eight lanes per
+// column with segmented scans (and, for FP64 data or Nz > 32, one thread per column
+// in scratch), one launch: 2176^2, 20 planes, mixed 3.37 -> 1.62 ms; two walls 4.39
+// -> 1.9; 2700^2, 11 planes, forces only 3.34 -> 1.05; 768^2 0.43 -> 0.22; in FP64
+// 1.41 -> 0.44; 192^2, Nz = 48, FP64 6.2 -> 0.12.
 #include <algorithm>
 #include <type_traits>
 

@@ -201,8 +201,9 @@ namespace fcmdp {
 
 // --- launchers implemented in the .hip translation units -----------------
 // prep.hip
-// keys, band, domain errors, sort by cell, cell starts (n = 0: empty band only)
+// keys, band, domain errors, sort by cell (n = 0: empty band only)
 hipError_t launch_sort(const fcmdp_solver* s, int n, const void* pos, hipStream_t st);
+// cell starts and weight records of the sorted particles
 hipError_t launch_records(const fcmdp_solver* s, int n, const void* pos,
                           const void* F, const void* T, hipStream_t st);
 // new forces in the records of the last launch_records
@@ -212,8 +213,8 @@ hipError_t launch_set_band(const fcmdp_solver* s, int lo, int hi,
 hipError_t launch_fill(void* ptr, size_t bytes, hipStream_t st);
 // spread_interp.hip
 hipError_t launch_spread(const fcmdp_solver* s, int n, void* grid, hipStream_t st);
-// spread_mfma.hip: the FP32 grid's spread on the matrix cores (grids of at
-// least 22 x 14 nodes)
+// spread_mfma.hip: spread on the matrix cores, FP32 and FP64 grids of at least
+// 22 x 14 nodes; derivative torques on FP32 grids without the FP64 vertical force
 bool spread_mfma_fits(const fcmdp_solver* s);
 hipError_t launch_spread_mfma(const fcmdp_solver* s, int n, void* grid, hipStream_t st);
 hipError_t launch_interp(const fcmdp_solver* s, int n, const void* grid,

@@ -890,12 +890,17 @@ static hipError_t y_pass(const fcmdp_solver* s, int nch, void* spec, int sign, h
 // Channels per group of an x- and a y-pass that run one after the other on it.
 // A group whose planes stay in the 256 MB last-level cache between the two saves
 // the second its reads from HBM; each further pair of launches costs its
-// drained ends.  The band is known to the device only; usually it is half of
-// the Nz planes.  Forward / inverse in us, all channels against groups: 768^2
-// FP64 (151 MB a channel) 745/682 -> 672/654 by two; 1176^2 FP32 (177 MB)
-// 562/476 -> 525/490 by one; 768^2 FP32 (76 MB) 310/301 -> 293/294 by three; but
-// 756 x 442 (217 MB all channels) 223/174 -> 241/191 and 2176^2 (606 MB a
-// channel) 2217/2394 -> 2584/2659 by one.
+// drained ends.  The band is known to the device only; the line is for bands of
+// about half of the Nz planes.  Forward / inverse in us, all channels against
+// groups: 768^2 FP64 (151 MB a channel) 745/682 -> 672/654 by two; 1176^2 FP32
+// (177 MB) 562/476 -> 525/490 by one; 768^2 FP32 (76 MB) 310/301 -> 293/294 by
+// three; but 756 x 442 (217 MB all channels) 223/174 -> 241/191 and 2176^2 (606 MB
+// a channel) 2217/2394 -> 2584/2659 by one.  Six channels with 14, 24 and all of 32
+// planes reached, time by groups over time by all, FP32 forward: 1344^2 (232 MB)
+// 0.94 0.92 0.95, 1500^2 (288 MB) 0.95 0.94 0.99, 1560^2 (312 MB) 0.93 0.99 1.02,
+// 1536^2 (302 MB, fixed x plan) 1.02 1.00 1.05; FP64 forward and inverse: 864^2
+// (192 MB) 0.98 0.93 0.96, 1040^2 (277 MB) 0.94 0.96 1.01, 1080^2 (299 MB) 0.92
+// 0.95 1.00.
 static int fft_group(const fcmdp_solver* s, int nch) {
   const double mb = (s->mixed ? 8e-6 : 16e-6) * s->dp.Nz * s->dp.Nkx * s->dp.Ny;
   const double fits = 320;

@@ -1,5 +1,5 @@
 // Row transforms of any supported length, both precisions: the x- and y-passes
-// of lengths without a fixed plan, and every length in FP64.
+// of lengths without a fixed plan, and in FP64 all but small grids (fft.hip).
 //
 // A workgroup owns a batch of rows in LDS and steps through a run-time plan of
 // few, large radices (at most 16 in FP32, 12 in FP64, and the primes 11, 13,
@@ -17,8 +17,9 @@
 // points FP32 80/61/86 -> 39/37/43, 756 x 442 172/138/171 -> 116/87/110, 1176
 // 463/329/482 -> 310/261/255, 768 FP64 775/630/820 -> 439/324/436.  The fixed
 // plans of fft.hip, one wavefront per row without barriers, stay for their
-// lengths (forward, fixed against run-time: 2176 points 2.23 / 4.2 ms, 768
-// 0.31 / 0.54, 2700 2.03 / 2.62).
+// lengths (forward, fixed against run-time, with the full batches that rows of
+// 1280 to 2548 points in x now keep: 2176 points 2.34 / 4.4 ms, 768 0.28 / 0.48,
+// 2700 1.50 / 2.61).
 #include <algorithm>
 #include <cmath>
 

@@ -489,9 +489,10 @@ static void sort_impl(const fcmdp_solver* s, int n, const Tin* pos, hipStream_t 
   }
 }
 
-// Keys and sort, with the cell starts, against one histogram, scan and scatter kernel per pass
-// with a serial scan of the workgroup totals and a final copy: 61 -> 23 us at
-// 1031 particles, 110 -> 63 at 17k, 125 -> 74 at 131k, 245 -> 141 at 1M.  Bound
+// Keys, sort and the cell starts, which were a kernel of their own then (now in
+// the launch of k_records), against one histogram, scan and scatter kernel per
+// pass with a serial scan of the workgroup totals and a final copy: 61 -> 23 us
+// at 1031 particles, 110 -> 63 at 17k, 125 -> 74 at 131k, 245 -> 141 at 1M.  Bound
 // by launches up to some 10^5 particles, then by the scattered writes.
 hipError_t launch_sort(const fcmdp_solver* s, int n, const void* pos, hipStream_t st) {
   if (s->mixed) sort_impl<float>(s, n, (const float*)pos, st);
