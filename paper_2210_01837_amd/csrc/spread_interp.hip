@@ -99,8 +99,8 @@ k_spread(DevParams dp, const int* __restrict__ band,
 }
 
 // Wave-uniform spread, where spread_mfma.hip does not go: derivative torques in
-// FP64 or with the vertical force in FP64, and grids smaller than a block's
-// region.  A wavefront owns an 8 x 8 patch of grid columns and
+// FP64 or with the vertical force in FP64, grids smaller than a block's region,
+// and few particles on an FP64 grid.  A wavefront owns an 8 x 8 patch of grid columns and
 // walks, in cell-sorted order, every particle of the 14 x 14 cells whose
 // kernels can reach the patch.  The particle is the same on all lanes; each
 // lane adds its contribution to its own column when that column lies in the
@@ -570,7 +570,17 @@ hipError_t launch_spread(const fcmdp_solver* s, int n, void* grid, hipStream_t s
   if (!s->force_simple_spread) {
     // without torques only the three force channels are spread
     const bool dip = s->dp.nch_in == 6;
-    if (!s->force_wave_spread && spread_mfma_fits(s))
+    // FP64 grids with fewer than one particle in 1024 cells: most patches of the
+    // gather meet no particle and only write zeros, while a workgroup of the
+    // matrix cores walks its whole strip (us, matrix cores / gather, with and
+    // without torques, one in 1000 cells: 192^2, 32 nodes 18/17 14/14, all planes
+    // 26/20 20/16; 338^2 x 48 64/31 39/20, 103/46 59/26; 1458 x 338 x 32 178/102
+    // 96/42, 300/220 161/71; 1500^2 x 16 306/287 135/108, 502/514 212/200; one in
+    // 250 cells: 192^2 18/19 15/15, 1500^2 x 16 290/309 134/114, 501/561 198/223).
+    // The FP64 vertical force is even there, from 0.8 to 1.9 by the grid.
+    const bool few = !s->mixed && (int64_t)n * 1024 <= s->dp.ncells &&
+                     s->spread_block_rows == 0;
+    if (!s->force_wave_spread && !few && spread_mfma_fits(s))
       return launch_spread_mfma(s, n, grid, st);
     if (s->mixed && s->dp.lowk_ns >= 0)
       dip ? spread_wave<float, 6, true>(s, grid, st)
