@@ -263,8 +263,8 @@ enum {
   FCMDP_VARIANT_SPREAD_BLOCK_ROWS = 12, /* grid rows per block of the
                                         matrix-core spread (8 or 16; 0 =
                                         default, chosen by particle density,
-                                        and the WAVE_SPREAD kernel for few
-                                        particles on an FP64 grid) */
+                                        and the WAVE_SPREAD kernel for few or
+                                        crowded particles on an FP64 grid) */
   FCMDP_VARIANT_SPREAD_ORDER = 13,   /* block order of the matrix-core
                                         spread: 1 strip-major, shared evenly;
                                         2 neighbouring strips side by side;

@@ -100,7 +100,7 @@ k_spread(DevParams dp, const int* __restrict__ band,
 
 // Wave-uniform spread, where spread_mfma.hip does not go: derivative torques in
 // FP64 or with the vertical force in FP64, grids smaller than a block's region,
-// and few particles on an FP64 grid.  A wavefront owns an 8 x 8 patch of grid columns and
+// and few or crowded particles on an FP64 grid.  A wavefront owns an 8 x 8 patch of grid columns and
 // walks, in cell-sorted order, every particle of the 14 x 14 cells whose
 // kernels can reach the patch.  The particle is the same on all lanes; each
 // lane adds its contribution to its own column when that column lies in the
@@ -578,9 +578,17 @@ hipError_t launch_spread(const fcmdp_solver* s, int n, void* grid, hipStream_t s
     // 96/42, 300/220 161/71; 1500^2 x 16 306/287 135/108, 502/514 212/200; one in
     // 250 cells: 192^2 18/19 15/15, 1500^2 x 16 290/309 134/114, 501/561 198/223).
     // The FP64 vertical force is even there, from 0.8 to 1.9 by the grid.
-    const bool few = !s->mixed && (int64_t)n * 1024 <= s->dp.ncells &&
-                     s->spread_block_rows == 0;
-    if (!s->force_wave_spread && !few && spread_mfma_fits(s))
+    // Crowded tall ones too, whose regions outgrow the ring and are staged again
+    // for every tile row and chunk of planes (one particle in 1.4 cells, lower half
+    // and all planes reached: 300^2 x 48 372/321 254/227, 550/331 377/242; 400^2 x
+    // 48 582/525 401/232, 876/615 599/275; 512^2 x 56 749/680 512/440, 1125/796
+    // 765/527; but 200^2 x 48 195/234 136/177, 512^2 x 40 386/588 262/373, and
+    // 300^2 x 48 with one in 2.5 188/186 130/136, 281/205 191/155).
+    const int64_t cells = s->dp.ncells;
+    const bool few = (int64_t)n * 1024 <= cells;
+    const bool crowded = s->dp.Nz > 40 && cells >= 80000 && 5 * (int64_t)n >= 3 * cells;
+    const bool gather = !s->mixed && (few || crowded) && s->spread_block_rows == 0;
+    if (!s->force_wave_spread && !gather && spread_mfma_fits(s))
       return launch_spread_mfma(s, n, grid, st);
     if (s->mixed && s->dp.lowk_ns >= 0)
       dip ? spread_wave<float, 6, true>(s, grid, st)

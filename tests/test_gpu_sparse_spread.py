@@ -1,6 +1,7 @@
-"""Spread of few particles on FP64 grids: the gather up to one particle in 1024
-cells, the matrix cores beyond it, and both block sizes of the latter there too.
-Tolerance 1e-13, as for the other FP64 spreads."""
+"""Spread of few and of crowded particles on FP64 grids.  Few: the gather up to one
+particle in 1024 cells, the matrix cores beyond it, and both block sizes of the
+latter there too.  Crowded, on tall grids: the gather from three particles in five
+cells on.  Tolerance 1e-13, as for the other FP64 spreads."""
 import numpy as np
 import pytest
 
@@ -34,4 +35,32 @@ def test_few_particles(geometry, nx, ny, nz, n, rows, torques):
     ref = oracle_spread(box, pos, F, T if torques else np.zeros_like(T))
     got = got.cpu().numpy()
     assert rel_err(got, ref) < 1e-13 and max_rel(got, ref) < 1e-13
+    s.close()
+
+
+@pytest.mark.parametrize("torques", [True, False])
+@pytest.mark.parametrize("nz,n,gather", [(41, 48384, True), (41, 48383, False),
+                                         (40, 48384, False)])
+def test_crowded_tall_grid(nz, n, gather, torques):
+    """Default against the gather (its bits where it is the default) and the matrix
+    cores."""
+    from paper_2210_01837_amd import Solver
+    box = Box("sc", 144.0, 140.0, 12.0, 288, 280, nz)
+    rng = np.random.default_rng(82)
+    dev = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda")   # noqa: E731
+    P = dev(rng.random((n, 3)) * [box.Lx, box.Ly, box.H])
+    F, T = dev(rng.standard_normal((n, 3))), dev(rng.standard_normal((n, 3)))
+    print(f"[crowded spread] Nz={nz} n={n} torques {torques}", flush=True)
+    s = Solver.from_box(box, precision="fp64", max_particles=n)
+    out = []
+    for name, value in ((None, 0), ("wave_spread", 1), ("spread_block_rows", 8)):
+        if name:
+            s.set_variant(name, value)
+        out.append(s.stage_spread(P, F, T if torques else None))
+        if name:
+            s.set_variant(name, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) == gather
+    for other in out[1:]:
+        assert float((out[0] - other).norm() / other.norm()) < 1e-13
     s.close()
